@@ -22,17 +22,24 @@
 //
 //  * Frames.  A frame is the candidate list of one search node: entry k carries its mask
 //    restricted to the frame's R, so a child's R' is simply the candidate's own mask.  When
-//    |R| <= 64 the masks are compressed to |R| bits (one word).  Each frame also holds
-//    inverted per-bit tables -- the paper's reverse scan turned into an index: for every bit
-//    b of R, the first list position with b, the number of entries with b, the sum of their
-//    L-side hash terms and the posting list of positions with b.
+//    |R| <= 64 the masks are compressed to |R| bits (one word).  Each frame also holds the
+//    paper's reverse scan turned into an index: for every bit b of R a row, the position bitmap
+//    of the entries with b, and tables of the first candidate with b, their number and the sum
+//    of their L-side hash terms.  Q entries are rows only.
 //
 //  * Nodes.  A candidate at position i with |R'| = 1 (almost every node on power-law
 //    graphs) is settled by one lookup: it is maximal exactly when the first entry with its
 //    bit is itself, and then L' is every entry with that bit.  The 64 lanes of a wave settle
-//    64 such candidates at once.  Candidates with |R'| >= 2 are handled by the whole wave:
-//    a maximality test on the rarest bit's posting list, and for maximal nodes one scan of
-//    the list that counts, compacts (ballot + prefix sum) and stably counting-sorts P'.
+//    64 such candidates at once, and test 64 candidates (or as many as the row words allow) of
+//    |R'| >= 2 for maximality at once.  What is left, the maximal nodes of |R'| >= 2, is
+//    expanded by the whole wave: one pass over R''s rows finds L', P' and Q'.
+//
+//    What bounds the search is the wave's instruction and dependent-access chain per node, not
+//    bandwidth (a tenth of HBM).  Measured on the power-law graph of 100,000 x 50,000 vertices
+//    and 10^6 edges: tests one node at a time, Q' as list entries with masks and shuffles through
+//    the LDS pipe 37.6 ms; the tests 64 at a time, Q' as rows (subsets of R' found by word ANDs
+//    when |R'| <= 6) and cross-lane moves on the vector pipe 21.0 ms.  Twelve top-level
+//    candidates of a 20,000 x 5,000 graph of 2M edges: 280 -> 68 ms.
 //
 //  * Second level (the paper's k = 2 subtrees): the waves of the workgroup claim 64-wide
 //    chunks of the top-level node's child list from an LDS counter; each wave then runs its
@@ -53,13 +60,15 @@ constexpr uint32_t kShared = 0xFFFFFFFFu;
 constexpr uint32_t kMovedMark = 1u << 30;  // added to the LDS item counter when the list moves  // frame offset meaning "the workgroup's top-level list"
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr int kQKeep = 256;      // most incomparable Q' masks a compressed child keeps
-// classes that reduce Q' through the presence word when |R'| <= 6 (the widest class runs out
-// of scalar registers with it)
-template <int W>
-constexpr bool kSmallRPrune = W <= 4;
-// A maximal node's listed entries (stu) stay in the wave's LDS for lists of at most this many
-// entries, in global scratch for longer ones.
+// A compressed child's Q' (entries with two or more bits of R') is reduced to its
+// inclusion-maximal masks when it has more than this many entries.  The reduction compares every
+// entry with the masks kept so far; below the line the AND of a few more row words per check
+// costs less.
+constexpr int kQReduce = 256;
+// A maximal node's P' positions (stu) stay in the wave's LDS for lists of at most this many
+// candidates, in global scratch for longer ones.
 constexpr int kStuLds = 256;
+static_assert(2 * kStuLds >= 64 * 8, "P' masks of 64 entries fit the second half");
 constexpr int kWaveLds = 1024 + 8 * kQKeep + 4 * kStuLds;  // LDS bytes per wave besides the histogram
 // The fixed-width classes keep a graph's rank bitmap and its popcount prefix in LDS, after the
 // waves' regions, when the bitmap has at most this many words (131,072 candidates); larger
@@ -104,40 +113,55 @@ __device__ __forceinline__ uint64_t uni(uint64_t x) {
 __device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, 63); }
 __device__ __forceinline__ uint64_t lanes_below() { return (1ull << lane_id()) - 1ull; }
 
+// Cross-lane moves on the vector pipe: DPP within rows of 16 lanes, the row and half swaps
+// between them.  (Shuffles through the LDS pipe are a round trip of some 60-100 cycles each,
+// six of them in a row for a reduction or a transpose, on the critical path of every node.)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+}
+
+// x of the lane CTRL names in the rows of mask ROWS, 0 elsewhere (shifts bring 0 in)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+// Inclusive scan with a commutative operation whose identity is 0: shifts by 1, 2, 4 and 8
+// within each row of 16, then lane 15 of rows 0 and 2 into the next row, lane 31 into the upper
+// half.  All 64 lanes are active.
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_scan32(uint32_t v, Op op) {
+    v = op(v, dpp_or_zero<0x111, 0xF>(v));
+    v = op(v, dpp_or_zero<0x112, 0xF>(v));
+    v = op(v, dpp_or_zero<0x114, 0xF>(v));
+    v = op(v, dpp_or_zero<0x118, 0xF>(v));
+    v = op(v, dpp_or_zero<0x142, 0xA>(v));
+    return op(v, dpp_or_zero<0x143, 0xC>(v));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_or_zero64(uint64_t x) {
+    return ((uint64_t)dpp_or_zero<CTRL, ROWS>((uint32_t)(x >> 32)) << 32) | dpp_or_zero<CTRL, ROWS>((uint32_t)x);
+}
+__device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+}
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return uni(v);
-}
-__device__ __forceinline__ int wave_sum_i32(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return uni(v);
-}
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t t = __shfl_xor(v, o);
-        v = t < v ? t : v;
-    }
-    return uni(v);
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t t = __shfl_xor(v, o);
-        v = t > v ? t : v;
-    }
-    return uni(v);
+    v += dpp_or_zero64<0x111, 0xF>(v);
+    v += dpp_or_zero64<0x112, 0xF>(v);
+    v += dpp_or_zero64<0x114, 0xF>(v);
+    v += dpp_or_zero64<0x118, 0xF>(v);
+    v += dpp_or_zero64<0x142, 0xA>(v);
+    v += dpp_or_zero64<0x143, 0xC>(v);
+    return readlane64(v, 63);
 }
 __device__ __forceinline__ int wave_incl_scan(int v) {
-    const int ln = lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(v, o);
-        if (ln >= o) v += t;
-    }
-    return v;
+    return (int)wave_scan32((uint32_t)v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ int wave_sum_i32(int v) { return last_lane(wave_incl_scan(v)); }
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    return (uint32_t)last_lane((int)wave_scan32(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }));
 }
 
 __device__ __forceinline__ uint32_t align2(uint32_t x) { return (x + 1u) & ~1u; }
@@ -205,8 +229,8 @@ __device__ __forceinline__ void bm_or(lds_u64 *p, uint64_t v) {
 struct FrameState {
     uint32_t off;    // 32-bit-word offset of the frame's data in the wave stack, or kShared
     uint32_t top;    // first free stack word above this frame
-    int32_t n;       // list length
-    int32_t nq;      // positions [0, nq) are the node's Q; candidates are [nq, n)
+    int32_t n;       // list positions: [0, nq) Q entries (rows only), [nq, n) the candidates
+    int32_t nq;
     int32_t level;   // search depth of the candidates taken from this list (top level = 1)
     int32_t nL;      // |L| of the nodes below
     int32_t wf;      // mask words per entry
@@ -216,6 +240,8 @@ struct FrameState {
     uint64_t heavy;  // lanes of the current chunk still to be handled one by one
     uint64_t sL;     // sum of the L-side hash terms of L
     uint64_t fw;     // sum over the list of (2 + deg v), byte tally only
+    int32_t nm;      // the method's |P| + |Q| of the list, tallies of diagnostics mode only
+    int32_t pad;
 };
 
 __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
@@ -233,17 +259,24 @@ __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
     u.heavy = uni(f.heavy);
     u.sL = uni(f.sL);
     u.fw = uni(f.fw);
+    u.nm = uni(f.nm);
+    u.pad = 0;
     return u;
 }
 
-// Word layout of a frame's data starting at a 2-aligned offset o:
-//   ids[n] | hs[n] (u64) | masks[n][wf] (u64) | first[64wf] | cnt[64wf] | H[64wf] (u64) |
-//   orig[64] | rows[rbits][nw] (u64), nw = ceil(n / 64)
-// ids are universe indices (kept for diagnostics), hs the L-side hash term of each entry.
-// Row b is the position bitmap of mask bit b: bit k % 64 of its word k / 64 is set when entry
-// k holds bit b; only bits [0, rbits) can be set (rbits = |R| for a compressed frame).
-// first / cnt / H: per bit, the first position holding it, how many entries hold it, and the
-// sum of their hash terms (valid for bits below rbits).
+// Word layout of a frame's data starting at a 2-aligned offset o (np = n - nq candidates):
+//   ids[n] | hs[np] (u64) | masks[np][wf] (u64) | first[64wf] | cnt[64wf] | H[64wf] (u64) |
+//   orig[64] | hR[64] (u64) | rows[rbits][nw] (u64), nw = ceil(n / 64)
+// ids are universe indices; a child frame has them in diagnostics mode only.  hs is the L-side
+// hash term and masks the mask of each candidate.  Row b is the position bitmap of mask bit b:
+// bit k % 64 of its word k / 64 is set when entry k holds bit b; only bits [0, rbits) can be
+// set (rbits = |R| for a compressed frame).  Q entries exist in the rows alone: all a Q entry
+// ever does is witness that some R'' below is not maximal, which is an AND of rows, so it
+// needs no mask, hash term or id of its own.
+// first / cnt / H: per bit, 1 + the first candidate position holding it, or 0 when some Q entry
+// holds it (a Q entry with a single bit of R witnesses nothing else: outside diagnostics mode it
+// is left out of the rows); how many candidates hold it, and the sum of their hash terms
+// (valid for bits below rbits).
 struct FrameView {
     const uint32_t *ids;
     const uint64_t *hs;
@@ -257,11 +290,11 @@ struct FrameView {
     int nw;
 };
 
-__device__ __forceinline__ uint32_t frame_words_fixed(int n, int wf, int rbits) {
-    const uint32_t bits = 64u * (uint32_t)wf, nw = ((uint32_t)n + 63u) >> 6;
-    uint32_t o = align2((uint32_t)n);
-    o += 2u * (uint32_t)n;                 // hs
-    o += 2u * (uint32_t)n * (uint32_t)wf;  // masks
+__device__ __forceinline__ uint32_t frame_words_fixed(int n, int nq, int wf, int rbits, bool ids) {
+    const uint32_t bits = 64u * (uint32_t)wf, nw = ((uint32_t)n + 63u) >> 6, np = (uint32_t)(n - nq);
+    uint32_t o = ids ? align2((uint32_t)n) : 0u;
+    o += 2u * np;                          // hs
+    o += 2u * np * (uint32_t)wf;           // masks
     o += 2u * bits;                        // first, cnt
     o += 2u * bits;                        // H
     o += 64u;                              // orig
@@ -270,16 +303,16 @@ __device__ __forceinline__ uint32_t frame_words_fixed(int n, int wf, int rbits) 
     return o;
 }
 
-__device__ __forceinline__ FrameView frame_view(uint32_t *base, int n, int wf, int rbits) {
-    const uint32_t bits = 64u * (uint32_t)wf;
+__device__ __forceinline__ FrameView frame_view(uint32_t *base, int n, int nq, int wf, bool ids) {
+    const uint32_t bits = 64u * (uint32_t)wf, np = (uint32_t)(n - nq);
     FrameView v;
     v.nw = (n + 63) >> 6;
     v.ids = base;
-    uint32_t o = align2((uint32_t)n);
+    uint32_t o = ids ? align2((uint32_t)n) : 0u;
     v.hs = reinterpret_cast<const uint64_t *>(base + o);
-    o += 2u * (uint32_t)n;
+    o += 2u * np;
     v.masks = reinterpret_cast<const uint64_t *>(base + o);
-    o += 2u * (uint32_t)n * (uint32_t)wf;
+    o += 2u * np * (uint32_t)wf;
     v.first = base + o;
     o += bits;
     v.cnt = base + o;
@@ -296,25 +329,33 @@ __device__ __forceinline__ FrameView frame_view(uint32_t *base, int n, int wf, i
 
 // 64 x 64 bit-matrix transpose across the wave: on entry lane i holds row i (bit j is element
 // (i, j)), on return lane j holds column j (bit i is element (i, j)).  Recursive block swap:
-// at block size s, the upper-right and lower-left s x s blocks trade places.
+// at block size s, the upper-right and lower-left s x s blocks trade places.  Size 32 swaps
+// register halves between the wave's halves, 16 and 8 move whole bytes (one byte permute each,
+// its selector depending on the lane), 4, 2 and 1 shift and merge.
 __device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
-    const int ln = lane_id();
-    const uint64_t keep[6] = {0x00000000FFFFFFFFull, 0x0000FFFF0000FFFFull, 0x00FF00FF00FF00FFull,
-                              0x0F0F0F0F0F0F0F0Full, 0x3333333333333333ull, 0x5555555555555555ull};
+    const uint32_t ln = (uint32_t)lane_id();
+    auto s32 = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)(x >> 32), false, false);
+    uint32_t h[2] = {(uint32_t)s32[0], (uint32_t)s32[1]};
+    // byte selectors: sources 0-3 are the second operand's bytes, 4-7 the first's
+    const uint32_t sel16 = (ln & 16u) ? 0x03020706u : 0x01000504u;  // odd rows keep the high halves
+    const uint32_t sel8 = (ln & 8u) ? 0x07030501u : 0x02060004u;
+    const bool b4 = ln & 4u, b2 = ln & 2u, b1 = ln & 1u;
 #pragma unroll
-    for (int l = 0; l < 6; ++l) {
-        const int sft = 32 >> l;
-        const uint64_t lo = keep[l];  // bits whose index has bit sft clear
-        const uint64_t y = __shfl_xor(x, sft);
-        x = (ln & sft) ? ((x & ~lo) | ((y & ~lo) >> sft)) : ((x & lo) | ((y & lo) << sft));
+    for (int q = 0; q < 2; ++q) {
+        uint32_t v = h[q];
+        auto s16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = __builtin_amdgcn_perm((uint32_t)s16[0], (uint32_t)s16[1], sel16);
+        uint32_t y = dpp_mov<0x128>(v);  // row_ror:8, lane ^ 8
+        v = __builtin_amdgcn_perm(v, y, sel8);
+        y = dpp_mov<0x1B>(dpp_mov<0x141>(v));  // half mirror, then quad mirror: lane ^ 4
+        v = b4 ? ((v & 0xF0F0F0F0u) | ((y >> 4) & 0x0F0F0F0Fu)) : ((v & 0x0F0F0F0Fu) | ((y << 4) & 0xF0F0F0F0u));
+        y = dpp_mov<0x4E>(v);  // lane ^ 2
+        v = b2 ? ((v & 0xCCCCCCCCu) | ((y >> 2) & 0x33333333u)) : ((v & 0x33333333u) | ((y << 2) & 0xCCCCCCCCu));
+        y = dpp_mov<0xB1>(v);  // lane ^ 1
+        v = b1 ? ((v & 0xAAAAAAAAu) | ((y >> 1) & 0x55555555u)) : ((v & 0x55555555u) | ((y << 1) & 0xAAAAAAAAu));
+        h[q] = v;
     }
-    return x;
-}
-
-// Rows [64q, 64q + 64) at word w of a frame, from mask word q of entries 64w .. 64w + 63
-// (x: this lane's entry's word, 0 past the end).  One wave.
-__device__ __forceinline__ void store_rows(const FrameView &v, int q, int w, uint64_t x) {
-    v.rows[(size_t)(64 * q + lane_id()) * v.nw + w] = wave_transpose64(x);
+    return ((uint64_t)h[1] << 32) | h[0];
 }
 
 struct Ctx {
@@ -330,7 +371,8 @@ struct Ctx {
     uint32_t *stu_l;                  // the same in this wave's LDS (lists of at most kStuLds entries)
     lds_u32 *tl_first, *tl_cnt;       // this wave's LDS tables for narrow children
     lds_u64 *tl_H;
-    lds_u64 *qk;                      // this wave's LDS list of kept Q' masks (kQKeep)
+    lds_u64 *qk;                      // this wave's LDS list of Q' masks (kQKeep)
+    lds_u64 *pm;                      // P' masks of a child list of at most 64 (the second half of stu_l)
     lds_u32 *hist;                    // this wave's LDS histogram
     int64_t scap;
     int32_t x_root, s0, c_is_v, Wroot;
@@ -420,75 +462,6 @@ __device__ __forceinline__ void wave_sort_by_key(const uint32_t *src, const uint
     }
 }
 
-// Per-bit tables and rows of a wide frame whose entries are in place; its masks lie within
-// the words of R (m): rows of the other words are never read and are not written.  One wave.
-template <int WF>
-__device__ __forceinline__ void build_tables_wide(const FrameView &v, int n, int nq, const uint64_t (&m)[WF]) {
-    constexpr int bits = 64 * WF;
-    const int ln = lane_id();
-    for (int b = ln; b < bits; b += 64) {
-        v.first[b] = kNone;
-        v.cnt[b] = 0u;
-        v.H[b] = 0ull;
-    }
-    wait_mem();
-    for (int base = 0; base < n; base += 64) {
-        const int k = base + ln;
-        const bool act = k < n;
-        const uint64_t h = act && k >= nq ? v.hs[k] : 0ull;  // Q entries carry no hash term
-#pragma unroll
-        for (int w = 0; w < WF; ++w) {
-            if (!m[w]) continue;  // uniform
-            const uint64_t x = act ? v.masks[(size_t)k * WF + w] : 0ull;
-            uint64_t y = x;
-            while (y) {
-                const int b = 64 * w + __ffsll((unsigned long long)y) - 1;
-                y &= y - 1ull;
-                atomicMin(&v.first[b], (uint32_t)k);
-                atomicAdd(&v.cnt[b], 1u);
-                atomicAdd(reinterpret_cast<unsigned long long *>(&v.H[b]), (unsigned long long)h);
-            }
-            store_rows(v, w, base >> 6, x);
-        }
-    }
-    see_atomics();
-}
-
-// Narrow frames (one mask word per entry) accumulate first / cnt / H in the wave's LDS
-// scratch while their entries are written (narrow_table_add); narrow_table_finish writes the
-// tables out and builds the rows.  One wave.
-__device__ __forceinline__ void narrow_table_clear(const Ctx &c) {
-    const int ln = lane_id();
-    c.tl_first[ln] = kNone;
-    c.tl_cnt[ln] = 0u;
-    c.tl_H[ln] = 0ull;
-    __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ void narrow_table_add(const Ctx &c, uint32_t slot, uint64_t m, uint64_t h) {
-    while (m) {
-        const int b = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1ull;
-        lds_min32(&c.tl_first[b], slot);
-        lds_add32(&c.tl_cnt[b], 1u);
-        lds_add64(&c.tl_H[b], h);
-    }
-}
-__device__ __forceinline__ void narrow_table_finish(const Ctx &c, const FrameView &v, int n, int r) {
-    const int ln = lane_id();
-    __builtin_amdgcn_wave_barrier();
-    if (ln < r) {
-        v.first[ln] = c.tl_first[ln];
-        v.cnt[ln] = c.tl_cnt[ln];
-        v.H[ln] = c.tl_H[ln];
-    }
-    for (int base = 0; base < n; base += 64) {
-        const int k = base + ln;
-        const uint64_t t = wave_transpose64(k < n ? v.masks[k] : 0ull);
-        if (ln < r) v.rows[(size_t)ln * v.nw + (base >> 6)] = t;
-    }
-    wait_mem();
-}
-
 // Write the record of the maximal biclique (L', R') of a node.  R' is given as positions of
 // N(x_root) (Rr, Wroot words).  L' = {x_root} u {universe v : M[v] contains R'}: every vertex
 // adjacent to all of R'.  Sides are sorted later by the canonicaliser.
@@ -539,11 +512,95 @@ __device__ __forceinline__ void write_record(const Ctx &c, const uint64_t *Rr, i
     }
 }
 
-// Candidates [base, base+64) of frame F: lanes with |R'| = 1 are settled here; the rest are
-// returned as a lane mask.
+// Maximality of the candidates of chunk base (lane l: position base + l, mask m) whose lanes are
+// in hv, |R'| >= 2, frames of one-word masks: a candidate is not maximal when an earlier entry
+// holds all of R', a bit below its position in the AND of R''s rows.  Returns the lanes that are
+// not maximal.  Most are not, and one such test alone leaves a wave waiting for a few words, so
+// the wave tests many at once: 2^lg lanes per candidate, one per row word up to the chunk's end
+// (lists of up to 64 entries: every lane its own candidate, the rows held one per lane).  Handled
+// one by one these tests took about a fifth of the power-law search and a third of the skewed
+// one's.
+template <bool DIAG, bool TB>
+__device__ __forceinline__ uint64_t check_chunk(const Ctx &c, const FrameState &F, const FrameView &v, int base,
+                                                uint64_t m, uint64_t hv, WaveAcc &acc, bool settle) {
+    const int ln = lane_id();
+    const bool mine = (hv >> ln) & 1ull;
+    const int words = min(v.nw, ((base + 63) >> 6) + 1);
+    bool dead = false;
+    if (words == 1) {
+        const uint64_t row = ln < F.rbits ? v.rows[(size_t)ln * v.nw] : 0ull;
+        uint64_t a = mine ? (1ull << ((base + ln) & 63)) - 1ull : 0ull;
+        uint64_t mm = mine ? m : 0ull;
+        while (__ballot(a != 0ull && mm != 0ull)) {
+            const int b = mm ? __ffsll((unsigned long long)mm) - 1 : 0;
+            const uint64_t x = __shfl(row, b);
+            if (mm) a &= x;
+            mm &= mm - 1ull;
+        }
+        dead = a != 0ull;
+    } else {
+        const int lg = words > 32 ? 6 : 32 - __clz(words - 1);
+        const int group = 1 << lg, per = 64 >> lg, nh = __popcll(hv), rk = __popcll(hv & lanes_below());
+        const int sub = ln & (group - 1), grp = ln >> lg;
+        if (mine) c.tl_cnt[rk] = (uint32_t)ln;  // (the table space is free between child builds)
+        __builtin_amdgcn_wave_barrier();
+        for (int done = 0; done < nh; done += per) {
+            const bool on = done + grp < nh;
+            const int src = on ? (int)c.tl_cnt[done + grp] : 0;
+            const uint64_t ms = __shfl(m, src);
+            const int i = base + src, wi = i >> 6;
+            bool hit = false;
+            for (int w0 = 0; w0 < words; w0 += group) {
+                const int wd = w0 + sub;
+                uint64_t a = on && !hit ? (wd < wi ? ~0ull : wd == wi ? (1ull << (i & 63)) - 1ull : 0ull) : 0ull;
+                uint64_t mm = ms;
+                while (__ballot(a != 0ull && mm != 0ull)) {
+                    if (a != 0ull && mm != 0ull) {
+                        const int b0 = __ffsll((unsigned long long)mm) - 1;
+                        mm &= mm - 1ull;
+                        const int b1 = mm ? __ffsll((unsigned long long)mm) - 1 : b0;
+                        mm &= mm - 1ull;
+                        const int b2 = mm ? __ffsll((unsigned long long)mm) - 1 : b0;
+                        mm &= mm - 1ull;
+                        a &= v.rows[(size_t)b0 * v.nw + wd] & v.rows[(size_t)b1 * v.nw + wd] &
+                             v.rows[(size_t)b2 * v.nw + wd];
+                    }
+                }
+                hit = hit || a != 0ull;
+            }
+            const uint64_t hb = __ballot(hit);
+            if (mine && rk >= done && rk < done + per)
+                dead = ((hb >> ((rk - done) << lg)) & (lg == 6 ? ~0ull : (1ull << group) - 1ull)) != 0ull;
+        }
+    }
+    if (settle) {
+        if (DIAG && dead) {
+            const int i = base + ln;
+            const uint64_t dx = deg_of(c, v.ids[i]);
+            uint64_t rs = 0;
+            for (uint64_t mm = m; mm; mm &= mm - 1ull)
+                rs += 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)(__ffsll((unsigned long long)mm) - 1))];
+            const uint64_t fw = F.fw - (2ull + dx);
+            acc.nodes += 1;
+            acc.nonmax += 1;
+            if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
+            acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + (uint64_t)__popcll(m));
+        }
+        // the row words up to the candidate (lists of up to 64: every row once)
+        if (TB && mine)
+            acc.dbytes += words == 1 ? 0ull : 8ull * (uint64_t)__popcll(m) * (uint64_t)(((base + ln) >> 6) + 1);
+        if (TB && ln == 0 && words == 1) acc.dbytes += 8ull * (uint64_t)F.rbits;
+    }
+    return __ballot(dead);
+}
+
+// Candidates [base, base+64) of frame F: lanes with |R'| = 1 are settled here; returned are the
+// lanes still to be handled one by one: |R'| >= 2, and for one-word masks maximal (with records
+// on, maximal candidates of |R'| = 1 too).
 template <int WF, bool DIAG, bool ENUM, bool TB = false>
 __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &F, const FrameView &v, int base, WaveAcc &acc,
                                 bool settle = true) {
+    const uint64_t t0 = DIAG ? clock64() : 0ull;
     const int ln = lane_id();
     const int i = base + ln;
     const bool act = i < F.n;
@@ -551,119 +608,122 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
     int r = 0;
 #pragma unroll
     for (int w = 0; w < WF; ++w) {
-        m[w] = act ? v.masks[(size_t)i * WF + w] : 0ull;
+        m[w] = act ? v.masks[(size_t)(i - F.nq) * WF + w] : 0ull;
         r += __popcll(m[w]);
     }
-    if (ENUM) return __ballot(act);
-    const bool light = settle && act && r == 1;
-    if (light) {
+    bool own = false;  // |R'| = 1 and maximal: no earlier entry holds its bit
+    if (act && r == 1) {
         int b = 0;
 #pragma unroll
         for (int w = 0; w < WF; ++w)
             if (m[w]) b = 64 * w + __ffsll((unsigned long long)m[w]) - 1;
-        const bool maximal = v.first[b] == (uint32_t)i;  // no earlier entry holds bit b
-        const uint32_t rp = root_pos(F, v, (uint32_t)b);
-        if (maximal) {
+        own = v.first[b] == (uint32_t)i + 1u;
+        if (settle && own && !ENUM) {
             // L' = L u {every entry with bit b}: all of them sit at positions >= i
             const uint64_t sL = F.sL + v.H[b];
             acc.count += 1;
             acc.hash += pair_hash(c.c_is_v, sL, root_hash(c, F, v, (uint32_t)b));
             acc.out_ints += 2ull + (uint64_t)F.nL + (uint64_t)v.cnt[b] + 1ull;
         }
-        if (DIAG) {
+        if (DIAG && settle && !(ENUM && own)) {
             acc.nodes += 1;
-            if (!maximal) acc.nonmax += 1;
+            if (!own) acc.nonmax += 1;
             if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
             const uint64_t dx = deg_of(c, v.ids[i]);
-            const uint64_t rs = 2ull + (uint64_t)c.degl[rp];
+            const uint64_t rs = 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)b)];
             const uint64_t fw = F.fw - (2ull + dx);
-            acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.n - 1) + 1ull);
+            acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + 1ull);
         }
         // first[b]; for a maximal node H[b], cnt[b], the R-side hash term (and orig[b])
-        if (TB) acc.dbytes += 4ull + (maximal ? 20ull : 0ull);
+        if (TB && settle) acc.dbytes += 4ull + (own ? 20ull : 0ull);
     }
     if (TB && act && settle) acc.dbytes += 8ull * WF;  // the entry's mask
-    return __ballot(act && r >= 2);
+    uint64_t hv = __ballot(act && r >= 2);
+    if (DIAG) acc.ph[PH_LIGHT] += clock64() - t0;
+    if constexpr (WF == 1) {
+        const uint64_t t1 = DIAG ? clock64() : 0ull;
+        if (hv) hv &= ~check_chunk<DIAG, TB>(c, F, v, base, m[0], hv, acc, settle);
+        if (DIAG) acc.ph[PH_CHECK] += clock64() - t1;
+    }
+    if (ENUM) hv |= __ballot(own);
+    return hv;
 }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// The compression of entry k's mask to the |R'| bits of R' (bit t = the t-th bit of R').
-template <int WF>
-__device__ __forceinline__ uint64_t compress_mask(const FrameView &v, const uint64_t (&m)[WF], int k) {
-    uint64_t out = 0;
-    int t = 0;
-#pragma unroll
-    for (int w = 0; w < WF; ++w) {
-        if (!m[w]) continue;  // uniform
-        uint64_t mm = m[w];
-        const uint64_t xx = v.masks[(size_t)k * WF + w];
-        while (mm) {  // the same trip count on every lane: m is uniform
-            const int p = __ffsll((unsigned long long)mm) - 1;
-            mm &= mm - 1ull;
-            out |= ((xx >> p) & 1ull) << t;
-            ++t;
+// Adds to sup the subsets SET u {t, ..}, t >= T, of R''s r bits that some Q entry holds: q[t] is
+// this lane's word of the Q positions holding bit t, a the AND of q over SET.  Supersets of a set
+// nobody holds are passed over.
+template <int T, uint32_t SET>
+__device__ __forceinline__ void q_subsets(const uint64_t (&q)[6], int r, uint64_t a, uint64_t &sup) {
+    if constexpr (T < 6) {
+        if (T < r) {
+            const uint64_t b = a & q[T];
+            if (__ballot(b != 0ull)) {
+                sup |= 1ull << (SET | (1u << T));
+                q_subsets<T + 1, (SET | (1u << T))>(q, r, b, sup);
+            }
+            q_subsets<T + 1, SET>(q, r, a, sup);
         }
     }
-    return out;
 }
 
-// Q' of a compressed child, reduced to its inclusion-maximal masks.  A Q entry only ever
-// serves as a witness that some later R'' (a subset of R') is not maximal, and an entry
-// whose mask over R' lies inside another's witnesses nothing the other does not, so only
-// one entry per maximal mask needs to stay.  The Q' entries are stu[0, qn); the kept
-// compressed masks go to c.qk.  Returns their number, or -1 when more than kQKeep are
-// incomparable (then nothing is dropped).  Cost per chunk of 64 entries: one pass over the
-// kept masks, and one over the chunk's candidates.
-template <int WF, bool SMALL_R>
-__device__ __forceinline__ int prune_q(const Ctx &c, const FrameView &v, const uint64_t (&m)[WF], int qn, int r,
-                                       const uint32_t *stu) {
+// Calls f(wd, y) for the 64-position words wd (below and at the one holding position i, without
+// the others; words < 64 only when in nzq) of a frame, where lane e of y is the mask, compressed
+// to R''s r bits, of the entry at position 64 wd + e (0 from position i on); bt is the frame bit
+// of R''s bit lane_id().  Row words are loaded four words at a time.  f returns whether to go on.
+template <typename Fn>
+__device__ __forceinline__ void each_q_word(const FrameView &v, int i, int r, uint32_t bt, uint64_t nzq, Fn f) {
+    const int ln = lane_id(), wi = i >> 6;
+    const uint64_t *row = v.rows + (size_t)bt * v.nw;
+    int next = 0;
+    auto step = [&]() {  // the next word to look at, or wi + 1
+        while (next <= wi) {
+            if (next >= 64) return next++;
+            const uint64_t rest = nzq >> next;
+            if (rest) {
+                next += __ffsll((unsigned long long)rest);
+                return next - 1;
+            }
+            next = 64;
+        }
+        return wi + 1;
+    };
+    bool go = true;
+    while (go) {
+        int wd[4];
+        uint64_t x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            wd[q] = step();
+            x[q] = ln < r && wd[q] <= wi ? row[wd[q]] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (!go || wd[q] > wi) {
+                go = false;
+                continue;
+            }
+            go = f(wd[q], wave_transpose64(wd[q] == wi ? x[q] & ((1ull << (i & 63)) - 1ull) : x[q]));
+        }
+    }
+}
+
+// Q' of a compressed child, reduced to its inclusion-maximal masks of two or more bits.  A Q
+// entry only ever serves as a witness that some later R'' (a subset of R') is not maximal, and
+// an entry whose mask over R' lies inside another's witnesses nothing the other does not, so
+// only one entry per maximal mask needs to stay.  The kept compressed masks go to c.qk.  Returns
+// their number, or -1 when more than kQKeep are incomparable (then nothing is dropped).  Cost
+// per 64 entries: one pass over the kept masks, and one over the word's candidates.
+__device__ __forceinline__ int reduce_q(const Ctx &c, const FrameView &v, int i, int r, uint32_t bt, uint64_t nzq) {
     const int ln = lane_id();
     const uint64_t below = lanes_below();
-    if (SMALL_R && r <= 6) {
-        // every compressed mask is a value below 64: the set of values present is one word,
-        // its superset closure takes six shift-and-mask rounds, and the maximal values are
-        // the present ones no strictly larger present value contains
-        uint64_t pres = 0;
-        for (int base = 0; base < qn; base += 64) {
-            const int j = base + ln;
-            if (j < qn) pres |= 1ull << compress_mask<WF>(v, m, (int)stu[j]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) pres |= __shfl_xor(pres, o);
-        pres = uni(pres);
-        // value T: some present S contains T (round t adds the sets that differ in bit t)
-        uint64_t sup = pres;
-        sup |= (sup >> 1) & 0x5555555555555555ull;
-        sup |= (sup >> 2) & 0x3333333333333333ull;
-        sup |= (sup >> 4) & 0x0F0F0F0F0F0F0F0Full;
-        sup |= (sup >> 8) & 0x00FF00FF00FF00FFull;
-        sup |= (sup >> 16) & 0x0000FFFF0000FFFFull;
-        sup |= (sup >> 32) & 0x00000000FFFFFFFFull;
-        // value T: some present S strictly contains T (T plus one more bit, then any superset)
-        const uint64_t above = ((sup >> 1) & 0x5555555555555555ull) | ((sup >> 2) & 0x3333333333333333ull) |
-                               ((sup >> 4) & 0x0F0F0F0F0F0F0F0Full) | ((sup >> 8) & 0x00FF00FF00FF00FFull) |
-                               ((sup >> 16) & 0x0000FFFF0000FFFFull) | ((sup >> 32) & 0x00000000FFFFFFFFull);
-        const uint64_t mx = pres & ~above;
-        if ((mx >> ln) & 1ull) c.qk[__popcll(mx & below)] = (uint64_t)ln;
-        __builtin_amdgcn_wave_barrier();
-        return __popcll(mx);
-    }
     int nk = 0;
-    for (int base = 0; base < qn; base += 64) {
-        const int j = base + ln;
-        const bool act = j < qn;
-        const uint64_t x = act ? compress_mask<WF>(v, m, (int)stu[j]) : 0ull;
-        bool cand = act;
+    each_q_word(v, i, r, bt, nzq, [&](int, uint64_t x) {
+        bool cand = __popcll(x) >= 2;
         for (int t = 0; t < nk; ++t) {
             const uint64_t y = c.qk[t];  // same address on every lane
             if ((x & ~y) == 0ull) cand = false;
         }
-        // among this chunk: drop x when another candidate holds more, or the same in a lower lane
+        // among this word: drop x when another candidate holds more, or the same in a lower lane
         bool keep = cand;
         for (uint64_t q = __ballot(cand); q; q &= q - 1ull) {
             const int l = __ffsll((unsigned long long)q) - 1;
@@ -671,7 +731,7 @@ __device__ __forceinline__ int prune_q(const Ctx &c, const FrameView &v, const u
             if (l != ln && (x & ~y) == 0ull && (x != y || l < ln)) keep = false;
         }
         const uint64_t sb = __ballot(keep);
-        if (!sb) continue;
+        if (!sb) return true;
         // kept masks inside a new survivor go (compacted in place, 64 at a time: an entry
         // only moves down, past entries already read); the survivors join
         int ns = 0;
@@ -690,89 +750,317 @@ __device__ __forceinline__ int prune_q(const Ctx &c, const FrameView &v, const u
             ns += __popcll(stb);
         }
         const int nn = ns + __popcll(sb);
-        if (nn > kQKeep) return -1;
+        if (nn > kQKeep) {
+            nk = -1;
+            return false;
+        }
         if (keep) c.qk[ns + __popcll(sb & below)] = x;
         __builtin_amdgcn_wave_barrier();
         nk = nn;
-    }
+        return true;
+    });
     return nk;
 }
 
-// Write the child frame of the maximal node at position i at the top of the wave's stack.
-// Its entries are the positions stu[0, nu) of the node's list, in list order: the first qn
-// (before i) form Q' and keep their order, the other pn (after i, 0 < |mask n R'| < |R'|)
-// form P', stably sorted by that count.  Each entry is written straight to its slot: c.hist
-// holds, per count, the number of P' entries (filled by the caller).  Masks are restricted
-// to R' and, when NARROW, compressed to |R'| bits; the tables and rows follow.  Sets the
-// layout fields of C; false when the stack is full.
-template <int WF, int W, bool NARROW, bool DIAG, bool TB = false>
-__device__ __forceinline__ bool build_child(const Ctx &c, const FrameState &F, const FrameView &v, const uint64_t (&m)[WF], int nu,
-                            int r, int qn, int pn, FrameState &C, int preq, WaveAcc &acc, bool tally,
-                            const uint32_t *stu) {
-    const bool stu_g = stu == c.stu;  // (design bytes: the listed entries are global only then)
-    const int ln = lane_id();
+// The maximal node a child list is built for: its position, R' and what the expansion found.
+template <int WF>
+struct Grown {
+    uint64_t m[WF];   // R', frame bits
+    int i, r;
+    int qn;           // Q' entries of two or more bits (diagnostics mode: all)
+    int pn;           // P' entries, their positions in stu[0, pn) in list order
+    uint64_t nzq;     // words (of the first 64) holding Q' entries
+    bool small;       // |R'| <= 6: sup holds the subsets of R' that Q' entries hold
+    uint64_t sup;
+    const uint32_t *stu;
+};
+
+// R''s bits of mask word x, compressed: bit t is the t-th bit of R' (m; t0: bits in earlier words).
+__device__ __forceinline__ uint64_t compress_word(uint64_t x, uint64_t m, int t0) {
+    uint32_t lo = 0, hi = 0;
+    for (int t = t0; m; m &= m - 1ull, ++t) {  // uniform
+        const int p = __ffsll((unsigned long long)m) - 1;
+        const uint32_t half = p < 32 ? (uint32_t)x : (uint32_t)(x >> 32);
+        const uint32_t bit = __builtin_amdgcn_ubfe(half, (uint32_t)p & 31u, 1u);
+        if (t < 32) lo |= bit << t;
+        else hi |= bit << (t - 32);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// The child list of a maximal node with |R'| <= 64, at the top of the wave's stack: its Q' as
+// position rows, then P' stably sorted by count, masks compressed to |R'| bits.  Q' entries are
+// read off the frame's rows, 64 at a time through a transpose.  Sets the layout fields of C;
+// false when the stack is full.  c.hist[0, r) holds the bits of R'.
+template <int WF, bool DIAG, bool TB>
+__device__ __forceinline__ bool build_narrow(const Ctx &c, const FrameState &F, const FrameView &v, const Grown<WF> &g,
+                                             FrameState &C, WaveAcc &acc, bool tally, uint64_t &fwc) {
+    const int ln = lane_id(), r = g.r, pn = g.pn;
     const uint64_t below = lanes_below();
-    int nzw = 0;  // words of R' (the mask words an entry's gathers read)
-#pragma unroll
-    for (int w = 0; w < WF; ++w) nzw += m[w] ? 1 : 0;
-    // Q': with diagnostics off, a compressed child keeps only its inclusion-maximal masks
-    // (the tallies of diagnostics mode count the full Q' of the method).  preq >= 0: the
-    // caller already left them in c.qk, and stu[0, pn) packs each P' entry's position (low
-    // 26 bits) with its compressed mask
-    int nq2 = qn;
-    bool pruned = false;
-    if (preq >= 0) {
-        nq2 = preq;
-        pruned = true;
-    } else if constexpr (NARROW && !DIAG) {
-        if (qn > 1) {
-            const int nk = prune_q<WF, kSmallRPrune<W>>(c, v, m, qn, r, stu);
-            if (TB && tally && ln == 0) acc.dbytes += (uint64_t)qn * ((stu_g ? 4ull : 0ull) + 8ull * (uint64_t)nzw);  // stu, masks
-            if (nk >= 0) {
-                nq2 = nk;
-                pruned = true;
-            }
+    const uint32_t bt = ln < r ? c.hist[ln] : 0u;
+    // each bit's position of N(x), R-side hash term, and whether an entry before the node holds it
+    uint32_t rp = 0, f1 = 0;
+    uint64_t rh = 0;
+    if (ln < r) {
+        rp = root_pos(F, v, bt);
+        rh = root_hash(c, F, v, bt);
+        f1 = v.first[bt];
+    }
+    // Q': with diagnostics off, reduced to its maximal masks where that pays
+    int nq2 = g.qn;
+    bool listed = false;  // the Q' masks are in c.qk
+    if (!DIAG && g.small) {
+        // a set is maximal when no set of one more bit is held; single bits are first[]'s
+        const uint64_t sup = g.sup;
+        const uint64_t above = ((sup >> 1) & 0x5555555555555555ull) | ((sup >> 2) & 0x3333333333333333ull) |
+                               ((sup >> 4) & 0x0F0F0F0F0F0F0F0Full) | ((sup >> 8) & 0x00FF00FF00FF00FFull) |
+                               ((sup >> 16) & 0x0000FFFF0000FFFFull) | ((sup >> 32) & 0x00000000FFFFFFFFull);
+        const uint64_t mx = sup & ~above & ~0x0000000100010116ull;
+        if ((mx >> ln) & 1ull) c.qk[__popcll(mx & below)] = (uint64_t)ln;
+        __builtin_amdgcn_wave_barrier();
+        nq2 = __popcll(mx);
+        listed = true;
+    } else if (!DIAG && g.qn > kQReduce) {
+        const int nk = reduce_q(c, v, g.i, r, bt, g.nzq);
+        if (nk >= 0) {
+            nq2 = nk;
+            listed = true;
         }
     }
-    const int n2 = nq2 + pn;
-    constexpr int wf2 = NARROW ? 1 : W;
+    const int n2 = nq2 + pn, nw2 = (n2 + 63) >> 6;
     const uint32_t off2 = F.top;
-    const int rbits2 = NARROW ? r : 64 * W;
-    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, wf2, rbits2));
+    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, nq2, 1, r, DIAG));
     if ((int64_t)top2 > c.scap) {
         if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_STACK_OVERFLOW);
         return false;
     }
     uint32_t *cb = c.stk + off2;
-    FrameView v2 = frame_view(cb, n2, wf2, rbits2);
-    uint32_t *ids2 = cb;
+    const FrameView v2 = frame_view(cb, n2, nq2, 1, DIAG);
     uint64_t *hs2 = const_cast<uint64_t *>(v2.hs);
     uint64_t *masks2 = const_cast<uint64_t *>(v2.masks);
-    if (NARROW) {
-        // orig2[t] = N(x_root) position of the t-th bit of R'
+    int c0 = 0;  // row words written so far; entries from 64 c0 on wait in c.qk
+    if (!listed && g.qn > 0) {
+        int held = 0;
+        each_q_word(v, g.i, r, bt, g.nzq, [&](int wd, uint64_t y) {
+            const bool sel = __popcll(y) >= (DIAG ? 1 : 2);
+            const uint64_t sb = __ballot(sel);
+            const int at = held + __popcll(sb & below);
+            if (sel) {
+                c.qk[at] = y;
+                if (DIAG) cb[64 * c0 + at] = v.ids[64 * wd + ln];
+            }
+            held += __popcll(sb);
+            __builtin_amdgcn_wave_barrier();
+            if (held >= 64) {
+                const uint64_t t = wave_transpose64(c.qk[ln]);
+                if (ln < r) v2.rows[(size_t)ln * nw2 + c0] = t;
+                const uint64_t z = c.qk[64 + ln];
+                __builtin_amdgcn_wave_barrier();
+                c.qk[ln] = z;
+                __builtin_amdgcn_wave_barrier();
+                held -= 64;
+                ++c0;
+            }
+            return true;
+        });
+    }
+    // P' entries to their slots: stably by count among the candidates
+    c.tl_H[ln] = 0ull;
+    __builtin_amdgcn_wave_barrier();
+    const int nbits = r <= 1 ? 1 : 32 - __clz(r - 1);
+    auto load_mask = [&](int k, bool act) {  // the entry's mask over R', compressed
+        uint64_t out = 0;
         int t0 = 0;
 #pragma unroll
         for (int w = 0; w < WF; ++w) {
-            const bool on = (m[w] >> ln) & 1ull;
-            const uint64_t bb = __ballot(on);
-            if (on) {
-                const int at = t0 + __popcll(bb & below);
-                v2.orig[at] = root_pos(F, v, (uint32_t)(64 * w + ln));
-                v2.hR[at] = root_hash(c, F, v, (uint32_t)(64 * w + ln));
-            }
-            t0 += __popcll(bb);
+            if (!g.m[w]) continue;  // uniform
+            out |= compress_word(act ? v.masks[(size_t)(k - F.nq) * WF + w] : 0ull, g.m[w], t0);
+            t0 += __popcll(g.m[w]);
         }
-        narrow_table_clear(c);
-        if (pruned) {
-            for (int t = ln; t < nq2; t += 64) {
-                const uint64_t x = c.qk[t];
-                masks2[t] = x;
-                narrow_table_add(c, (uint32_t)t, x, 0ull);
+        return out;
+    };
+    auto place = [&](int slot, int k, uint64_t cm) {
+        const uint64_t h = v.hs[k - F.nq];
+        masks2[slot] = cm;
+        hs2[slot] = h;
+        if (DIAG) {
+            const uint32_t li = v.ids[k];
+            cb[nq2 + slot] = li;
+            fwc += 2ull + deg_of(c, li);
+        }
+        for (uint64_t mm = cm; mm; mm &= mm - 1ull) lds_add64(&c.tl_H[__ffsll((unsigned long long)mm) - 1], h);
+    };
+    if (pn <= 64) {
+        // one entry per lane: its slot is the number of entries of a smaller count, and of the
+        // same count in lower lanes
+        const bool act = ln < pn;
+        const int k = act ? (int)g.stu[ln] : F.nq;
+        const uint64_t cm = load_mask(k, act);
+        const int cnt = __popcll(cm);
+        uint64_t lt = 0ull, same = __ballot(act);
+        for (int bit = nbits - 1; bit >= 0; --bit) {
+            const bool on = (cnt >> bit) & 1;
+            const uint64_t bb = __ballot(act && on);
+            lt |= on ? same & ~bb : 0ull;
+            same &= on ? bb : ~bb;
+        }
+        if (act) {
+            const int slot = __popcll(lt) + __popcll(same & below);
+            c.pm[slot] = cm;
+            place(slot, k, cm);
+        }
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __builtin_amdgcn_wave_barrier();
+        c.hist[ln] = 0u;  // (counts are below r <= 64)
+        __builtin_amdgcn_wave_barrier();
+        for (int base = 0; base < pn; base += 64) {
+            const int j = base + ln;
+            if (j < pn) {
+                const int k = (int)g.stu[j];
+                int cnt = 0;
+#pragma unroll
+                for (int w = 0; w < WF; ++w)
+                    if (g.m[w]) cnt += __popcll(v.masks[(size_t)(k - F.nq) * WF + w] & g.m[w]);  // words of R' only
+                lds_add32(&c.hist[cnt], 1u);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        {
+            const int h = (int)c.hist[ln];
+            const int incl = wave_incl_scan(h);
+            c.hist[ln] = (uint32_t)(incl - h);
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (int base = 0; base < pn; base += 64) {
+            const int j = base + ln;
+            const bool act = j < pn;
+            const int k = act ? (int)g.stu[j] : F.nq;
+            const uint64_t cm = load_mask(k, act);
+            const int cnt = __popcll(cm);
+            // stable placement among equal counts: lanes with the same count, in lane order
+            uint64_t same = __ballot(act);
+            for (int bit = 0; bit < nbits; ++bit) {
+                const bool on = (cnt >> bit) & 1;
+                const uint64_t bb = __ballot(act && on);
+                same &= on ? bb : ~bb;
+            }
+            uint32_t start = 0;
+            if (act) start = c.hist[cnt];
+            __builtin_amdgcn_wave_barrier();
+            if (act) {
+                if ((same >> ln) == 1ull) c.hist[cnt] = start + (uint32_t)__popcll(same);
+                place((int)start + __popcll(same & below), k, cm);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        wait_mem();  // masks2 is read by other lanes below
+    }
+    // the rest of the rows (the Q' tail, then P'), and each bit's first candidate and count
+    uint32_t first = kNone, cnt = 0;
+    for (int q = c0; q < nw2; ++q) {
+        const int p = 64 * q + ln;
+        uint64_t x = 0ull;
+        if (p < nq2) x = c.qk[p - 64 * c0];
+        else if (p < n2) x = pn <= 64 ? c.pm[p - nq2] : masks2[p - nq2];
+        const uint64_t t = wave_transpose64(x);
+        if (ln < r) v2.rows[(size_t)ln * nw2 + q] = t;
+        const int nqb = nq2 - 64 * q;  // Q' entries among this word's
+        const uint64_t tp = nqb <= 0 ? t : nqb >= 64 ? 0ull : t & (~0ull << nqb);
+        if (first == kNone && tp) first = (uint32_t)(64 * q + __ffsll((unsigned long long)tp));
+        cnt += (uint32_t)__popcll(tp);
+    }
+    if (ln < r) {
+        v2.first[ln] = f1 < (uint32_t)g.i + 1u ? 0u : first;
+        v2.cnt[ln] = cnt;
+        v2.H[ln] = c.tl_H[ln];
+        v2.orig[ln] = rp;
+        v2.hR[ln] = rh;
+    }
+    wait_mem();
+    if (TB && tally && ln == 0) {
+        // Q' rows read (unless the subsets gave it), each P' entry's mask words over R' and hash
+        // term in, mask and hash term out; tables, orig and hR in and out; rows
+        int nzw = 0;
+#pragma unroll
+        for (int w = 0; w < WF; ++w) nzw += g.m[w] ? 1 : 0;
+        acc.dbytes += (g.small ? 0ull : 8ull * (uint64_t)r * (uint64_t)((g.i >> 6) + 1)) +
+                      (uint64_t)pn * ((pn <= 64 ? 8ull : 16ull) * (uint64_t)nzw + 24ull) + 44ull * (uint64_t)r +
+                      8ull * (uint64_t)r * (uint64_t)nw2;
+    }
+    C.off = off2;
+    C.top = top2;
+    C.n = n2;
+    C.nq = nq2;
+    C.wf = 1;
+    C.narrow = 1;
+    C.chunk = nq2 - 64;
+    C.rbits = r;
+    C.heavy = 0ull;
+    return true;
+}
+
+// The child list of a maximal node with |R'| > 64: masks keep the frame's W words, Q' is the
+// frame's rows of R' up to the node, position for position, and P' follows from there.
+template <int W, bool DIAG, bool TB>
+__device__ __forceinline__ bool build_wide(const Ctx &c, const FrameState &F, const FrameView &v, const Grown<W> &g,
+                                           FrameState &C, WaveAcc &acc, bool tally, uint64_t &fwc) {
+    constexpr int bits = 64 * W;
+    const int ln = lane_id(), r = g.r, pn = g.pn, wi = g.i >> 6;
+    const uint64_t below = lanes_below();
+    const int nq2 = g.i, n2 = nq2 + pn, nw2 = (n2 + 63) >> 6;
+    const uint32_t off2 = F.top;
+    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, nq2, W, bits, DIAG));
+    if ((int64_t)top2 > c.scap) {
+        if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_STACK_OVERFLOW);
+        return false;
+    }
+    uint32_t *cb = c.stk + off2;
+    const FrameView v2 = frame_view(cb, n2, nq2, W, DIAG);
+    uint64_t *hs2 = const_cast<uint64_t *>(v2.hs);
+    uint64_t *masks2 = const_cast<uint64_t *>(v2.masks);
+    for (int base = 0; base < wi; base += 64) {
+        const int wd = base + ln;
+        for (int t = 0; t < r; t += 4) {
+            uint32_t b[4];
+            uint64_t x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[q] = uni(c.hist[t + q < r ? t + q : t]);
+            if (wd < wi) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = v.rows[(size_t)b[q] * v.nw + wd];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v2.rows[(size_t)b[q] * nw2 + wd] = x[q];
             }
         }
     }
-    // first slot of each count among the P' entries
-    int carry = nq2;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const int b = 64 * w + ln;
+        const bool in = (g.m[w] >> ln) & 1ull;
+        v2.first[b] = in && v.first[b] < (uint32_t)g.i + 1u ? 0u : kNone;
+        v2.cnt[b] = 0u;
+        v2.H[b] = 0ull;
+    }
+    if (DIAG)
+        for (int p = ln; p < nq2; p += 64) cb[p] = v.ids[p];
+    wait_mem();
+    __builtin_amdgcn_wave_barrier();
+    for (int b = ln; b < r; b += 64) c.hist[b] = 0u;  // counts are below r
+    __builtin_amdgcn_wave_barrier();
+    for (int base = 0; base < pn; base += 64) {
+        const int j = base + ln;
+        if (j < pn) {
+            const int k = (int)g.stu[j];
+            int cnt = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                if (g.m[w]) cnt += __popcll(v.masks[(size_t)(k - F.nq) * W + w] & g.m[w]);  // words of R' only
+            lds_add32(&c.hist[cnt], 1u);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    int carry = 0;
     for (int base = 0; base < r; base += 64) {
         const int b = base + ln;
         const int h = b < r ? (int)c.hist[b] : 0;
@@ -781,113 +1069,93 @@ __device__ __forceinline__ bool build_child(const Ctx &c, const FrameState &F, c
         carry += last_lane(incl);
     }
     __builtin_amdgcn_wave_barrier();
-    const int nbits = r <= 1 ? 1 : 32 - __clz(r - 1);
-    for (int base = pruned ? qn : 0; base < nu; base += 64) {
+    const int nbits = 32 - __clz(r - 1);
+    uint64_t tbits = 0;
+    for (int base = 0; base < pn; base += 64) {
         const int j = base + ln;
-        const bool act = j < nu;
-        const uint32_t e = act ? stu[j] : 0u;
-        const int k = preq >= 0 ? (int)(e & 0x3FFFFFFu) : (int)e;
-        uint64_t x[WF];
+        const bool act = j < pn;
+        const int k = act ? (int)g.stu[j] : F.nq;
+        uint64_t x[W];
         int cnt = 0;
-        if (preq >= 0) {
 #pragma unroll
-            for (int w = 0; w < WF; ++w) x[w] = 0ull;
-            cnt = __popc(e >> 26);
-        } else {
-#pragma unroll
-            for (int w = 0; w < WF; ++w) {
-                x[w] = act && m[w] ? v.masks[(size_t)k * WF + w] & m[w] : 0ull;  // words of R' only
-                cnt += __popcll(x[w]);
-            }
+        for (int w = 0; w < W; ++w) {
+            x[w] = act && g.m[w] ? v.masks[(size_t)(k - F.nq) * W + w] & g.m[w] : 0ull;
+            cnt += __popcll(x[w]);
         }
-        const bool inp = act && j >= qn;
-        uint32_t slot = (uint32_t)j;  // Q' entries keep their list order
-        if (__ballot(inp)) {
-            // stable placement among equal counts: lanes with the same count, in lane order
-            uint64_t same = __ballot(inp);
-            for (int bit = 0; bit < nbits; ++bit) {
-                const bool on = (cnt >> bit) & 1;
-                const uint64_t bb = __ballot(inp && on);
-                same &= on ? bb : ~bb;
-            }
-            uint32_t start = 0;
-            if (inp) start = c.hist[cnt];
-            __builtin_amdgcn_wave_barrier();
-            if (inp) {
-                slot = start + (uint32_t)__popcll(same & below);
-                if ((same >> ln) == 1ull) c.hist[cnt] = start + (uint32_t)__popcll(same);
-            }
-            __builtin_amdgcn_wave_barrier();
+        // stable placement among equal counts: lanes with the same count, in lane order
+        uint64_t same = __ballot(act);
+        for (int bit = 0; bit < nbits; ++bit) {
+            const bool on = (cnt >> bit) & 1;
+            const uint64_t bb = __ballot(act && on);
+            same &= on ? bb : ~bb;
         }
+        uint32_t start = 0;
+        if (act) start = c.hist[cnt];
+        __builtin_amdgcn_wave_barrier();
         if (act) {
-            if (DIAG) ids2[slot] = v.ids[k];
-            // Q entries' hash terms are never read (a node whose bit some Q entry holds is
-            // not maximal), so they are not copied
-            const uint64_t h = inp ? v.hs[k] : 0ull;
-            if (inp) hs2[slot] = h;
-            if (NARROW) {
-                uint64_t out = 0;
-                if (preq >= 0) {
-                    out = (uint64_t)(e >> 26);
-                } else {
-                    int t = 0;
-#pragma unroll
-                    for (int w = 0; w < WF; ++w) {
-                        uint64_t mm = m[w];
-                        while (mm) {  // the same trip count on every lane: m is uniform
-                            const int p = __ffsll((unsigned long long)mm) - 1;
-                            mm &= mm - 1ull;
-                            out |= ((x[w] >> p) & 1ull) << t;
-                            ++t;
-                        }
-                    }
-                }
-                masks2[slot] = out;
-                narrow_table_add(c, slot, out, h);
-            } else {
-#pragma unroll
-                for (int w = 0; w < WF; ++w) masks2[(size_t)slot * W + w] = x[w];
+            if ((same >> ln) == 1ull) c.hist[cnt] = start + (uint32_t)__popcll(same);
+            const uint32_t slot = start + (uint32_t)__popcll(same & below);
+            const uint64_t h = v.hs[k - F.nq];
+            hs2[slot] = h;
+            if (DIAG) {
+                const uint32_t li = v.ids[k];
+                cb[nq2 + (int)slot] = li;
+                fwc += 2ull + deg_of(c, li);
             }
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                masks2[(size_t)slot * W + w] = x[w];
+                uint64_t y = x[w];
+                while (y) {
+                    const int b = 64 * w + __ffsll((unsigned long long)y) - 1;
+                    y &= y - 1ull;
+                    atomicMin(&v2.first[b], (uint32_t)nq2 + slot + 1u);
+                    atomicAdd(&v2.cnt[b], 1u);
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&v2.H[b]), (unsigned long long)h);
+                }
+            }
+            tbits += (uint64_t)cnt;
         }
+        __builtin_amdgcn_wave_barrier();
+    }
+    see_atomics();
+    // the word holding the node's position on: Q' below it, then P'
+    const int sh = g.i & 63;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        if (!g.m[w]) continue;  // uniform: rows of the other words are never read
+        const size_t b = (size_t)(64 * w + ln);
+        uint64_t carry = (g.m[w] >> ln) & 1ull ? v.rows[b * v.nw + wi] & ((1ull << sh) - 1ull) : 0ull;
+        int q = 0;
+        for (; 64 * q < pn; ++q) {
+            const int e = 64 * q + ln;
+            const uint64_t t = wave_transpose64(e < pn ? masks2[(size_t)e * W + w] : 0ull);
+            v2.rows[b * nw2 + wi + q] = carry | (t << sh);
+            carry = sh ? t >> (64 - sh) : 0ull;
+        }
+        if (wi + q < nw2) v2.rows[b * nw2 + wi + q] = carry;
     }
     wait_mem();
-    if (TB && tally && ln == 0) {
-        const uint64_t nloop = (uint64_t)(nu - (pruned ? qn : 0));
-        uint64_t b = nloop * ((stu_g ? 4ull : 0ull) + 8ull * (uint64_t)wf2) + 16ull * (uint64_t)pn;  // stu; child masks; hs in and out
-        if (preq < 0) b += nloop * 8ull * (uint64_t)nzw;                           // the entries' masks over R'
-        if (NARROW) {
-            b += 8ull * (uint64_t)(pruned ? nq2 : 0) + 4ull * (uint64_t)r * (F.narrow ? 2ull : 1ull) +  // kept Q'; orig
-                 16ull * (uint64_t)r;                                                                    // hR
-            b += 16ull * (uint64_t)r + 8ull * (uint64_t)n2 + 8ull * (uint64_t)r * (uint64_t)v2.nw;   // tables; rows
-        } else {
-            // tables cleared, each entry's hash term and mask words read, its bits' table atomics
-            // (tallied per lane below), rows of the words of R'
-            b += 16ull * 64ull * W + (uint64_t)n2 * (8ull + 8ull * (uint64_t)nzw) +
-                 8ull * 64ull * (uint64_t)nzw * (uint64_t)v2.nw;
-        }
-        acc.dbytes += b;
-    }
-    if constexpr (NARROW) {
-        narrow_table_finish(c, v2, n2, r);
-    } else {
-        static_assert(WF == W, "wide children come from wide lists");
-        build_tables_wide<W>(v2, n2, nq2, m);
-        if (TB && tally)
-            for (int k = ln; k < n2; k += 64) {
-                uint64_t bits = 0;
+    if (TB && tally) {
+        // Q' rows in and out; tables cleared, each P' entry's mask words over R' (for the count
+        // and the placement), hash term in, both out, its bits' table atomics; its rows
+        int nzw = 0;
 #pragma unroll
-                for (int w = 0; w < W; ++w) bits += (uint64_t)__popcll(masks2[(size_t)k * W + w]);
-                acc.dbytes += 16ull * bits;
-            }
+        for (int w = 0; w < W; ++w) nzw += g.m[w] ? 1 : 0;
+        acc.dbytes += 16ull * tbits;
+        if (ln == 0)
+            acc.dbytes += 16ull * (uint64_t)r * (uint64_t)wi + 8ull * (uint64_t)r + 16ull * bits +
+                          (uint64_t)pn * (16ull + 24ull * (uint64_t)nzw + 8ull * W) +
+                          8ull * 64ull * (uint64_t)nzw * (uint64_t)(nw2 - wi);
     }
     C.off = off2;
     C.top = top2;
     C.n = n2;
     C.nq = nq2;
-    C.wf = wf2;
-    C.narrow = NARROW ? 1 : 0;
+    C.wf = W;
+    C.narrow = 0;
     C.chunk = nq2 - 64;
-    C.rbits = rbits2;
+    C.rbits = bits;
     C.heavy = 0ull;
     return true;
 }
@@ -913,260 +1181,213 @@ __device__ __forceinline__ void fold_rows(const Ctx &c, const FrameView &v, int 
     if (!in) a = 0ull;
 }
 
-// The candidate at position i of frame F, |R'| = r >= 1, handled by the whole wave.
-// Returns true when a child frame was written (its state in C).  report = false rebuilds the
-// child frame of a node another wave owns: nothing is counted or recorded.
+// What handling a node did: nothing below it, its child frame pushed (state in C), or a child
+// frame that did not fit the stack.  The caller learns of a full stack from here alone: looking
+// at the launch's flag word after every node was a round trip to the L2 on nearly every node
+// (most push nothing).
+enum class Node : int { kLeaf, kPushed, kFull };
+
+// The candidate at position i of frame F, |R'| = r >= 1, handled by the whole wave (one-word
+// masks: known to be maximal, see light_chunk).  report = false rebuilds the child frame of a
+// node another wave owns: nothing is counted or recorded.
 template <int WF, int W, bool DIAG, bool ENUM, bool TB = false>
-__device__ __forceinline__ bool heavy_node(const Ctx &c, const FrameState &F, const FrameView &v, int i, FrameState &C,
+__device__ __forceinline__ Node heavy_node(const Ctx &c, const FrameState &F, const FrameView &v, int i, FrameState &C,
                            WaveAcc &acc, bool report) {
     const int ln = lane_id();
     const uint64_t below = lanes_below();
-    uint64_t m[WF];
+    Grown<WF> g;
     int r = 0;
 #pragma unroll
     for (int w = 0; w < WF; ++w) {
-        m[w] = uni(v.masks[(size_t)i * WF + w]);  // R' (uniform)
-        r += __popcll(m[w]);
+        g.m[w] = uni(v.masks[(size_t)(i - F.nq) * WF + w]);  // R' (uniform)
+        r += __popcll(g.m[w]);
     }
-
     // the bits of R', ascending, in c.hist[0, r)
     {
         int t0 = 0;
 #pragma unroll
         for (int w = 0; w < WF; ++w) {
-            const bool on = (m[w] >> ln) & 1ull;
-            const uint64_t bb = __ballot(on);
-            if (on) c.hist[t0 + __popcll(bb & below)] = (uint32_t)(64 * w + ln);
-            t0 += __popcll(bb);
+            const bool on = (g.m[w] >> ln) & 1ull;
+            if (on) c.hist[t0 + __popcll(g.m[w] & below)] = (uint32_t)(64 * w + ln);
+            t0 += __popcll(g.m[w]);
         }
         __builtin_amdgcn_wave_barrier();
     }
-
-    // maximality: an earlier entry holding every bit of R' ends the node -- a position below
-    // i in the AND of R''s rows.  If some bit of R' first appears at i itself, nothing
-    // earlier can hold R'.
-    bool first_here = false;
-#pragma unroll
-    for (int w = 0; w < WF; ++w)
-        if (((m[w] >> ln) & 1ull) && v.first[64 * w + ln] == (uint32_t)i) first_here = true;
-    bool nonmax = false;
     uint64_t tp = DIAG ? clock64() : 0ull;
-    if (TB && report && ln == 0) acc.dbytes += 8ull * WF + 4ull * (uint64_t)r;  // R'; first[] of its bits
-    if (!__ballot(first_here)) {
-        const int wl = i >> 6;  // the word holding position i
-        for (int base = 0; base <= wl; base += 64) {
-            const int wd = base + ln;
-            uint64_t u, a;
-            fold_rows(c, v, r, wd, wd <= wl, u, a);
-            if (TB && report && ln == 0) acc.dbytes += 8ull * (uint64_t)r * (uint64_t)min(64, wl + 1 - base);
-            if (wd == wl) a &= (1ull << (i & 63)) - 1ull;
-            if (__ballot(a != 0ull)) {
-                nonmax = true;
-                break;
-            }
-        }
-    }
-
     uint64_t dx = 0, rs = 0;
-    if (DIAG) {
-        const uint64_t now = clock64();
-        acc.ph[PH_CHECK] += now - tp;
-        tp = now;
-        dx = deg_of(c, v.ids[i]);
-        uint64_t t = 0;
+    if constexpr (WF > 1) {
+        // maximality: an earlier entry holding every bit of R' ends the node -- a position below
+        // i in the AND of R''s rows.  If some bit of R' first appears at i itself, nothing
+        // earlier can hold R'.
+        bool first_here = false;
 #pragma unroll
         for (int w = 0; w < WF; ++w)
-            if ((m[w] >> ln) & 1ull) t += 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)(64 * w + ln))];
-        rs = wave_sum_u64(t);
-        if (ln == 0 && report) {
-            acc.nodes += 1;
-            if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
+            if (((g.m[w] >> ln) & 1ull) && v.first[64 * w + ln] == (uint32_t)i + 1u) first_here = true;
+        bool nonmax = false;
+        if (TB && report && ln == 0) acc.dbytes += 8ull * WF + 4ull * (uint64_t)r;  // R'; first[] of its bits
+        if (!__ballot(first_here)) {
+            const int wl = i >> 6;  // the word holding position i
+            for (int base = 0; base <= wl; base += 64) {
+                const int wd = base + ln;
+                uint64_t u, a;
+                fold_rows(c, v, r, wd, wd <= wl, u, a);
+                if (TB && report && ln == 0) acc.dbytes += 8ull * (uint64_t)r * (uint64_t)min(64, wl + 1 - base);
+                if (wd == wl) a &= (1ull << (i & 63)) - 1ull;
+                if (__ballot(a != 0ull)) {
+                    nonmax = true;
+                    break;
+                }
+            }
         }
-    }
-    if (nonmax) {
-        if (DIAG && ln == 0 && report) {
-            acc.nonmax += 1;
-            const uint64_t fw = F.fw - (2ull + dx);
-            acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.n - 1) + (uint64_t)r);
+        if (DIAG) {
+            const uint64_t now = clock64();
+            acc.ph[PH_CHECK] += now - tp;
+            tp = now;
         }
-        return false;
+        if (nonmax) {
+            if (DIAG && report) {
+                dx = deg_of(c, v.ids[i]);
+                uint64_t t = 0;
+#pragma unroll
+                for (int w = 0; w < WF; ++w)
+                    if ((g.m[w] >> ln) & 1ull) t += 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)(64 * w + ln))];
+                rs = wave_sum_u64(t);
+                if (ln == 0) {
+                    acc.nodes += 1;
+                    acc.nonmax += 1;
+                    if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
+                    const uint64_t fw = F.fw - (2ull + dx);
+                    acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + (uint64_t)r);
+                }
+            }
+            return Node::kLeaf;
+        }
+    } else {
+        if (TB && report && ln == 0) acc.dbytes += 8ull;  // R'
     }
 
-    // maximal.  Per word of positions: the OR of R''s rows gives the entries sharing a bit
-    // with R', the AND those holding all of it (after i only, the node being maximal; they
-    // join L').  The rest -- Q' before i, P' after -- are listed in stu in list order, and
-    // the P' counts |mask n R'| are tallied per value in c.hist for the child's stable sort.
-    //
-    // When |R'| <= 6 (and diagnostics are off) the rows give each entry's compressed mask
-    // directly (its bit in each of R''s rows), so no entry is read: Q' is reduced to its
-    // maximal masks through the presence word (as in prune_q) and only P' is listed, each
-    // stu word packing the position (low 26 bits) with the compressed mask.
-    int qn = 0, nu = 0;
-    // the listed entries (at most F.n - 1): in the wave's LDS when they fit
-    uint32_t *const stu = F.n <= kStuLds ? c.stu_l : c.stu;
-    int ne_l = 0, qn_l = 0;
-    uint64_t exps = 0, fwc = 0;
-    // (the two-word class takes it on its own two-word lists only: register budget)
-    const bool fastq = !DIAG && kSmallRPrune<W> && (W != 2 || WF == W) && r <= 6 && F.n < (1 << 26);
-    int preq = -1;  // with fastq: the number of maximal Q' masks left in c.qk
-    if (fastq) {
-        int bl[6];  // the bits of R'
-#pragma unroll
-        for (int t = 0; t < 6; ++t) bl[t] = t < r ? (int)uni(c.hist[t]) : 0;
-        __builtin_amdgcn_wave_barrier();
-        for (int b = ln; b < r; b += 64) c.hist[b] = 0u;
-        __builtin_amdgcn_wave_barrier();
+    // maximal.  Per word of positions: the OR of R''s rows gives the entries sharing a bit with
+    // R', the AND those holding all of it (after i only, the node being maximal; they join L').
+    // Of the rest, P' (after i) is listed in stu in list order.  Q' (before i) is only located:
+    // for |R'| <= 6 the subsets of R' that its entries hold are found by ANDs of whole row words,
+    // otherwise the entries holding two or more bits of R' are counted per word.
+    int ne_l = 0, qn_l = 0, nu = 0;
+    uint64_t exps = 0, fwc = 0, sup = 0, nzq = 0;
+    bool joins = false;
+    // (the two-word class's and wider top-level lists take all of it too)
+    const bool small = !DIAG && r <= 6;
+    uint32_t *const stu = F.n - F.nq <= kStuLds ? c.stu_l : c.stu;
+    {
         const int wi = i >> 6;
         const uint64_t bi = 1ull << (i & 63);
-        uint64_t pres = 0;
         for (int base = 0; base < v.nw; base += 64) {
             const int wd = base + ln;
             const bool in = wd < v.nw;
-            uint64_t x[6];
-            uint64_t u = 0ull, a = in ? ~0ull : 0ull;
-#pragma unroll
-            for (int t = 0; t < 6; ++t) {
-                x[t] = (t < r && in) ? v.rows[(size_t)bl[t] * v.nw + wd] : 0ull;
-                if (t < r) {
-                    u |= x[t];
-                    a &= x[t];
-                }
-            }
-            if (wd == wi) {
-                u &= ~bi;
-                a &= ~bi;
-            }
-            ne_l += __popcll(a);
-            for (uint64_t f = a; f;) {
-                const int b = __ffsll((unsigned long long)f) - 1;
-                f &= f - 1ull;
-                exps += v.hs[64 * wd + b];
-            }
-            const uint64_t qp = u & ~a;
             const uint64_t before = wd < wi ? ~0ull : (wd == wi ? bi - 1ull : 0ull);
-            auto cmask = [&](int p) {
-                uint32_t cm = 0;
+            uint64_t u = 0ull, a = in ? ~0ull : 0ull;
+            if (small) {
+                uint64_t x[6];
+#pragma unroll
+                for (int t = 0; t < 6; ++t) {
+                    x[t] = 0ull;
+                    if (t < r) {
+                        const uint32_t b = uni(c.hist[t]);
+                        if (in) x[t] = v.rows[(size_t)b * v.nw + wd];
+                    }
+                }
 #pragma unroll
                 for (int t = 0; t < 6; ++t)
-                    if (t < r) cm |= (uint32_t)((x[t] >> p) & 1ull) << t;
-                return cm;
-            };
-            for (uint64_t q = qp & before; q; q &= q - 1ull) pres |= 1ull << cmask(__ffsll((unsigned long long)q) - 1);
-            uint64_t pm = qp & ~before;
-            const int pc = __popcll(pm);
-            const int incl = wave_incl_scan(pc);
-            int at = nu + incl - pc;
-            while (pm) {
-                const int b = __ffsll((unsigned long long)pm) - 1;
-                pm &= pm - 1ull;
-                const uint32_t cm = cmask(b);
-                stu[at++] = (uint32_t)(64 * wd + b) | (cm << 26);
-                lds_add32(&c.hist[__popc(cm)], 1u);
-            }
-            nu += last_lane(incl);
-        }
+                    if (t < r) {
+                        u |= x[t];
+                        a &= x[t];
+                        x[t] &= before;
+                    }
+                if (base <= wi) q_subsets<0, 0u>(x, r, ~0ull, sup);
+            } else {
+                uint64_t tw = 0ull;
+                for (int t = 0; t < r; t += 4) {
+                    uint32_t b[4];
+                    uint64_t x[4];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) pres |= __shfl_xor(pres, o);
-        pres = uni(pres);
-        uint64_t sup = pres;
-        sup |= (sup >> 1) & 0x5555555555555555ull;
-        sup |= (sup >> 2) & 0x3333333333333333ull;
-        sup |= (sup >> 4) & 0x0F0F0F0F0F0F0F0Full;
-        sup |= (sup >> 8) & 0x00FF00FF00FF00FFull;
-        sup |= (sup >> 16) & 0x0000FFFF0000FFFFull;
-        sup |= (sup >> 32) & 0x00000000FFFFFFFFull;
-        const uint64_t above = ((sup >> 1) & 0x5555555555555555ull) | ((sup >> 2) & 0x3333333333333333ull) |
-                               ((sup >> 4) & 0x0F0F0F0F0F0F0F0Full) | ((sup >> 8) & 0x00FF00FF00FF00FFull) |
-                               ((sup >> 16) & 0x0000FFFF0000FFFFull) | ((sup >> 32) & 0x00000000FFFFFFFFull);
-        const uint64_t mx = pres & ~above;
-        if ((mx >> ln) & 1ull) c.qk[__popcll(mx & below)] = (uint64_t)ln;
-        preq = __popcll(mx);
-        qn = 0;
-        wait_mem();  // stu is read by other lanes below
-        __builtin_amdgcn_wave_barrier();
-    } else {
-        const int wi = i >> 6;
-        const uint64_t bi = 1ull << (i & 63);
-        for (int base = 0; base < v.nw; base += 64) {
-            const int wd = base + ln;
-            uint64_t u, a;
-            fold_rows(c, v, r, wd, wd < v.nw, u, a);
+                    for (int q = 0; q < 4; ++q) b[q] = uni(c.hist[t + q < r ? t + q : t]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) x[q] = in ? v.rows[(size_t)b[q] * v.nw + wd] : 0ull;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (t + q < r) tw |= u & x[q];
+                        u |= x[q];
+                        a &= x[q];
+                    }
+                }
+                const uint64_t qs = (DIAG ? u : tw) & before;
+                qn_l += __popcll(qs);
+                const uint64_t qb = __ballot(qs != 0ull);
+                if (base == 0) nzq = qb;
+                if (DIAG)
+                    for (uint64_t f = qs; f; f &= f - 1ull)
+                        fwc += 2ull + deg_of(c, v.ids[64 * wd + __ffsll((unsigned long long)f) - 1]);
+            }
             if (wd == wi) {
                 u &= ~bi;
                 a &= ~bi;
             }
-            ne_l += __popcll(a);
-            for (uint64_t f = a; f;) {
-                const int b = __ffsll((unsigned long long)f) - 1;
-                f &= f - 1ull;
-                exps += v.hs[64 * wd + b];
+            if (__ballot(a != 0ull)) {
+                joins = true;
+                ne_l += __popcll(a);
+                for (uint64_t f = a; f; f &= f - 1ull)
+                    exps += v.hs[64 * wd + __ffsll((unsigned long long)f) - 1 - F.nq];
             }
-            uint64_t qp = u & ~a;
-            qn_l += __popcll(qp & (wd < wi ? ~0ull : (wd == wi ? bi - 1ull : 0ull)));
-            const int pc = __popcll(qp);
-            const int incl = wave_incl_scan(pc);
-            int at = nu + incl - pc;
-            while (qp) {
-                const int b = __ffsll((unsigned long long)qp) - 1;
-                qp &= qp - 1ull;
-                stu[at++] = (uint32_t)(64 * wd + b);
-            }
-            nu += last_lane(incl);
-        }
-        qn = wave_sum_i32(qn_l);
-        wait_mem();  // stu is read by other lanes below
-        for (int b = ln; b < r; b += 64) c.hist[b] = 0u;
-        __builtin_amdgcn_wave_barrier();
-        for (int base = DIAG ? 0 : qn; base < nu; base += 64) {
-            const int j = base + ln;
-            if (j < nu) {
-                const int k = (int)stu[j];
-                if (j >= qn) {
-                    int cnt = 0;
-#pragma unroll
-                    for (int w = 0; w < WF; ++w)
-                        if (m[w]) cnt += __popcll(v.masks[(size_t)k * WF + w] & m[w]);  // words of R' only
-                    lds_add32(&c.hist[cnt], 1u);
+            uint64_t pm = u & ~a & ~before;
+            const uint64_t pw = __ballot(pm != 0ull);
+            if (__popcll(pw) <= 8) {
+                // few words: one at a time, a lane per position
+                for (uint64_t q = pw; q; q &= q - 1ull) {
+                    const int l = __ffsll((unsigned long long)q) - 1;
+                    const uint64_t y = readlane64(pm, l);
+                    if ((y >> ln) & 1ull) stu[nu + __popcll(y & below)] = (uint32_t)(64 * (base + l) + ln);
+                    nu += __popcll(y);
                 }
-                if (DIAG) fwc += 2ull + deg_of(c, v.ids[k]);
+            } else {
+                const int pc = __popcll(pm);
+                const int incl = wave_incl_scan(pc);
+                int at = nu + incl - pc;
+                for (; pm; pm &= pm - 1ull) stu[at++] = (uint32_t)(64 * wd + __ffsll((unsigned long long)pm) - 1);
+                nu += last_lane(incl);
             }
         }
     }
-    const int ne = wave_sum_i32(ne_l);
-    const int pn = nu - qn;
+    const int pn = nu;
+    const int ne = joins ? wave_sum_i32(ne_l) : 0;
+    const int qn = small ? 0 : wave_sum_i32(qn_l);
+    wait_mem();  // stu is read by other lanes below
     if (TB && report && ln == 0) {
-        // R''s rows over every word of positions, the joiners' hash terms, the listed entries
-        // (written, and for the counts of P' read back with their mask words over R'),
-        // the R-side hash terms (and orig) of R'
-        int nzw = 0;
-#pragma unroll
-        for (int w = 0; w < WF; ++w) nzw += m[w] ? 1 : 0;
-        const uint64_t sb = stu == c.stu ? 4ull : 0ull;  // (listed entries in global scratch)
-        uint64_t b = 8ull * (uint64_t)r * (uint64_t)v.nw + 8ull * (uint64_t)ne + sb * (uint64_t)nu;
-        if (!fastq) b += (uint64_t)pn * (sb + 8ull * (uint64_t)nzw);
-        b += (uint64_t)r * 8ull;
-        acc.dbytes += b;
+        // R''s rows over every word of positions, the joiners' hash terms, the listed P' entries
+        // (in global scratch: written and read back), the R-side hash terms of R'
+        acc.dbytes += 8ull * (uint64_t)r * (uint64_t)v.nw + 8ull * (uint64_t)ne +
+                      (stu == c.stu ? 8ull : 0ull) * (uint64_t)nu + (uint64_t)r * 8ull;
     }
 
     // report (L', R')
-    const uint64_t sL = F.sL + v.hs[i] + wave_sum_u64(exps);
-    uint64_t sr = 0;
-#pragma unroll
-    for (int w = 0; w < WF; ++w)
-        if ((m[w] >> ln) & 1ull) sr += root_hash(c, F, v, (uint32_t)(64 * w + ln));
-    sr = wave_sum_u64(sr);
+    const uint64_t sL = F.sL + v.hs[i - F.nq] + (joins ? wave_sum_u64(exps) : 0ull);
     const int nL = F.nL + 1 + ne;
-    if (ln == 0 && report) {
-        acc.count += 1;
-        acc.hash += pair_hash(c.c_is_v, sL, sr);
-        acc.out_ints += 2ull + (uint64_t)nL + (uint64_t)r;
+    if (report) {
+        uint64_t sr = 0;
+#pragma unroll
+        for (int w = 0; w < WF; ++w)
+            if ((g.m[w] >> ln) & 1ull) sr += root_hash(c, F, v, (uint32_t)(64 * w + ln));
+        sr = wave_sum_u64(sr);
+        if (ln == 0) {
+            acc.count += 1;
+            acc.hash += pair_hash(c.c_is_v, sL, sr);
+            acc.out_ints += 2ull + (uint64_t)nL + (uint64_t)r;
+        }
     }
     if (ENUM && report) {
         uint64_t Rr[16];
         for (int w = 0; w < 16; ++w) Rr[w] = 0ull;
 #pragma unroll
         for (int w = 0; w < WF; ++w) {
-            uint64_t mm = m[w];
+            uint64_t mm = g.m[w];
             while (mm) {
                 const int b = 64 * w + __ffsll((unsigned long long)mm) - 1;
                 mm &= mm - 1ull;
@@ -1176,34 +1397,54 @@ __device__ __forceinline__ bool heavy_node(const Ctx &c, const FrameState &F, co
         }
         write_record(c, Rr, nL, r);
     }
-    if (DIAG && ln == 0 && report) {
-        const uint64_t fw = F.fw - (2ull + dx);
-        acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.n - 1) + (uint64_t)r + (uint64_t)pn +
-                             (uint64_t)qn);
+    if (DIAG && report) {
+        dx = deg_of(c, v.ids[i]);
+        uint64_t t = 0;
+#pragma unroll
+        for (int w = 0; w < WF; ++w)
+            if ((g.m[w] >> ln) & 1ull) t += 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)(64 * w + ln))];
+        rs = wave_sum_u64(t);
+        if (ln == 0) {
+            acc.nodes += 1;
+            if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
+            const uint64_t fw = F.fw - (2ull + dx);
+            acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + (uint64_t)r + (uint64_t)pn +
+                                 (uint64_t)qn);
+        }
     }
     if (DIAG) {
         const uint64_t now = clock64();
         acc.ph[PH_EXPAND] += now - tp;
         tp = now;
     }
-    if (pn == 0) return false;
+    if (pn == 0) return Node::kLeaf;
 
     // child frame: Q' then P' stably sorted by count; masks restricted to R' and, when
     // |R'| <= 64, compressed to |R'| bits
+    g.i = i;
+    g.r = r;
+    g.qn = qn;
+    g.pn = pn;
+    g.nzq = nzq;
+    g.small = small;
+    g.sup = sup;
+    g.stu = stu;
     bool ok;
     if constexpr (WF == 1) {
-        ok = build_child<1, W, true, DIAG, TB>(c, F, v, m, nu, r, qn, pn, C, preq, acc, report, stu);
+        ok = build_narrow<1, DIAG, TB>(c, F, v, g, C, acc, report, fwc);
     } else {
-        ok = r <= 64 ? build_child<WF, W, true, DIAG, TB>(c, F, v, m, nu, r, qn, pn, C, preq, acc, report, stu)
-                     : build_child<WF, W, false, DIAG, TB>(c, F, v, m, nu, r, qn, pn, C, preq, acc, report, stu);
+        ok = r <= 64 ? build_narrow<WF, DIAG, TB>(c, F, v, g, C, acc, report, fwc)
+                     : build_wide<WF, DIAG, TB>(c, F, v, g, C, acc, report, fwc);
     }
-    if (!ok) return false;
+    if (!ok) return Node::kFull;
     C.level = F.level + 1;
     C.nL = nL;
     C.sL = sL;
     C.fw = DIAG ? wave_sum_u64(fwc) : 0ull;
+    C.nm = qn + pn;
+    C.pad = 0;
     if (DIAG) acc.ph[PH_CHILD] += clock64() - tp;
-    return true;
+    return Node::kPushed;
 }
 
 // A wave's third-level sharing state (kept in LDS: it is needed only between chunks).
@@ -1243,7 +1484,6 @@ struct WGShared {
     int slot;   // arena slot held by this workgroup
     int scan[16];
     unsigned long long red[16];  // per-graph tally reduction
-    unsigned long long cov[16];  // bits of N(x) held by a multi-bit top-level Q mask
     int held;            // the workgroup counts in a.busy
     int roots_done;      // this launch's top-level candidates are all handed out
     uint32_t busyw;      // waves holding work in the current task
@@ -1448,7 +1688,7 @@ __device__ __forceinline__ bool find_shared_list(const SearchArgs &a, WGShared *
 // hide it.
 // TB (with DIAG and ENUM off): the production search, also tallying its design bytes.
 template <int W, bool DIAG, bool ENUM, bool TB = false>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 : 2))) void search_kernel(SearchArgs a, int64_t lo, int64_t hi, unsigned int *counter) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !DIAG ? 4 : 2))) void search_kernel(SearchArgs a, int64_t lo, int64_t hi, unsigned int *counter) {
     extern __shared__ unsigned char lds_raw[];
     WGShared *sh = reinterpret_cast<WGShared *>(lds_raw);
     const int tid = threadIdx.x, nt = blockDim.x, wid = uni(tid >> 6), nw = nt >> 6, ln = lane_id();
@@ -1508,6 +1748,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
         c.tl_H = lds_at<lds_u64>(lds_raw, tb + 512);
         c.qk = lds_at<lds_u64>(lds_raw, tb + 1024);
         c.stu_l = reinterpret_cast<uint32_t *>(lds_raw + tb + 1024 + 8 * kQKeep);
+        c.pm = lds_at<lds_u64>(lds_raw, tb + 1024 + 8 * kQKeep + 2 * kStuLds);
     }
     // the rank bitmap and its prefix: in LDS when the launch's graphs are small enough
     const bool rl = a.dims.nwords <= kRankLdsWords;
@@ -1602,8 +1843,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
 #pragma unroll 1
                 for (int kind = 0; kind < 2 && !found; ++kind) {
                     const bool on = kind == 0 ? a.steal_on != 0 : k3;
-                    if (!on || __hip_atomic_load(kind == 0 ? a.steal_live : a.pub_live, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT) == 0u)
+                    // (one lane's value for all: others change it meanwhile, and the lanes of this
+                    // wave must not part here)
+                    if (!on || uni(__hip_atomic_load(kind == 0 ? a.steal_live : a.pub_live, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) == 0u)
                         continue;
                     char *arr = kind == 0 ? reinterpret_cast<char *>(a.steal) : reinterpret_cast<char *>(a.pub);
                     const int total = kind == 0 ? a.nslots : a.nslots * a.pubw;
@@ -1987,49 +2230,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
             continue;
         }
         // -- Q1 of the list: the universe entries ranked before x (all of them meet N(x)).
-        //    With diagnostics off, a single-bit mask is dropped when a Q1 mask of two or more
-        //    bits holds its bit, and of the other single-bit masks only the first per bit is
-        //    kept: a Q entry only witnesses that some R (a subset of N(x)) is not maximal, and
-        //    the dropped ones witness nothing the kept ones do not.  The count stays nq0 in
-        //    the tallies of diagnostics mode, which keep the method's full Q1.  Lists of up
-        //    to 256 are kept whole: there the pass's workgroup barriers cost more than the
-        //    shorter child lists save (measured).
+        //    With diagnostics off, a single-bit mask is dropped: such an entry only witnesses
+        //    that R = its bit is not maximal, which the bit's first[] entry says (0 below).  The
+        //    count stays nq0 in the tallies of diagnostics mode, which keep the method's full
+        //    Q1.  Lists of up to 256 are kept whole: there the pass's workgroup barriers cost
+        //    more than the shorter rows save (measured).
         uint32_t *ids1 = s1;
-        if (!DIAG && nq0 > 256) {
-            lds_u32 *first1 = lds_at<lds_u32>(lds_raw, sizeof(WGShared));  // BITS words
-            for (int b = tid; b < BITS; b += nt) first1[b] = kNone;
-            if (tid < W) sh->cov[tid] = 0ull;
-            __syncthreads();
-            for (int li = tid; li < nq0; li += nt)
-                if (cnt1[li] >= 2u) {
-#pragma unroll 1
-                    for (int w = 0; w < W; ++w) {
-                        const uint64_t y = M[(size_t)li * W + w];
-                        if (y) lds_or(&sh->cov[w], y);
-                    }
-                }
-            __syncthreads();
-            auto single_bit = [&](int li) {
-                int b = 0;
-#pragma unroll 1
-                for (int w = 0; w < W; ++w) {
-                    const uint64_t y = M[(size_t)li * W + w];
-                    if (y) b = 64 * w + __ffsll((unsigned long long)y) - 1;
-                }
-                return b;
-            };
-            for (int li = tid; li < nq0; li += nt)
-                if (cnt1[li] == 1u) {
-                    const int b = single_bit(li);
-                    if (!((sh->cov[b >> 6] >> (b & 63)) & 1ull)) lds_min32(&first1[b], (uint32_t)li);
-                }
-            __syncthreads();
+        const bool drop1 = !DIAG && nq0 > 256;
+        if (drop1) {
             const int nwq = (nq0 + 63) >> 6;
             for (int q = wid; q < nwq; q += nw) {
                 const int li = 64 * q + ln;
-                bool keep = false;
-                if (li < nq0) keep = cnt1[li] >= 2u || first1[single_bit(li)] == (uint32_t)li;
-                const uint64_t kb = __ballot(keep);
+                const uint64_t kb = __ballot(li < nq0 && cnt1[li] >= 2u);
                 if (ln == 0) hb[q] = kb;
             }
             wait_mem();
@@ -2054,7 +2266,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
 
         // -- the top-level child list as a frame: ids Q1 (earlier ranks) ++ P1 sorted by
         //    count, masks over the positions of N(x), per-bit tables
-        FrameView v1 = frame_view(s1, n1, W, d);
+        FrameView v1 = frame_view(s1, n1, nqk, W, true);
         if (wid == 0) {
             int pn = 0;
             for (int base = nq0; base < s0; base += 64) {
@@ -2090,22 +2302,35 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
         uint64_t *hs1 = const_cast<uint64_t *>(v1.hs);
         for (int j = tid; j < n1; j += nt) {
             const uint32_t li = ids1[j];
-            const uint64_t h = hl(c, gid[li]);
-            hs1[j] = h;
-            const uint64_t ht = j < nqk ? 0ull : h;  // Q entries carry no hash term
+            const bool cand = j >= nqk;
+            const uint64_t h = cand ? hl(c, gid[li]) : 0ull;
+            if (cand) hs1[j - nqk] = h;
 #pragma unroll 1
             for (int w = 0; w < W; ++w) {
                 uint64_t mm = M[(size_t)li * W + w];
-                masks1[(size_t)j * W + w] = mm;
+                if (cand) masks1[(size_t)(j - nqk) * W + w] = mm;
                 while (mm) {
                     const int b = 64 * w + __ffsll((unsigned long long)mm) - 1;
                     mm &= mm - 1ull;
-                    lds_min32(&lfirst[b], (uint32_t)j);
-                    lds_add32(&lcnt[b], 1u);
-                    lds_add64(&lH[b], ht);
+                    lds_min32(&lfirst[b], cand ? (uint32_t)j + 1u : 0u);
+                    if (cand) {
+                        lds_add32(&lcnt[b], 1u);
+                        lds_add64(&lH[b], h);
+                    }
                 }
             }
         }
+        if (drop1)
+            for (int li = tid; li < nq0; li += nt)
+                if (cnt1[li] == 1u) {
+                    int b = 0;
+#pragma unroll 1
+                    for (int w = 0; w < W; ++w) {
+                        const uint64_t y = M[(size_t)li * W + w];
+                        if (y) b = 64 * w + __ffsll((unsigned long long)y) - 1;
+                    }
+                    lds_min32(&lfirst[b], 0u);
+                }
         __syncthreads();
         for (int b = tid; b < BITS; b += nt) {
             v1.first[b] = lfirst[b];
@@ -2117,7 +2342,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
         for (int job = wid; job < v1.nw * qd; job += nw) {
             const int w = job / qd, q = job - w * qd;
             const int j = 64 * w + ln;
-            const uint64_t t = wave_transpose64(j < n1 ? masks1[(size_t)j * W + q] : 0ull);
+            const uint64_t t = wave_transpose64(j < n1 ? M[(size_t)ids1[j] * W + q] : 0ull);
             if (64 * q + ln < d) v1.rows[(size_t)(64 * q + ln) * v1.nw + w] = t;
         }
         wait_mem();
@@ -2141,11 +2366,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
         top.heavy = 0ull;
         top.sL = hl(c, x) + sh->exps;
         top.fw = uni((uint64_t)sh->fw1);
+        top.nm = nq0 + P1;
+        top.pad = 0;
         const int nch = thief3 ? 0 : (P1 + 63) >> 6;  // a third-level thief takes no top-level item
         for (int q = wid; q < nch; q += nw) {
-            const uint64_t tl = DIAG ? clock64() : 0ull;
             const uint64_t hm = light_chunk<W, DIAG, ENUM, TB>(c, top, v1, nqk + 64 * q, acc, !thief);
-            if (DIAG) acc.ph[PH_LIGHT] += clock64() - tl;
             if (ln == 0) hb[q] = hm;
         }
         wait_mem();
@@ -2168,12 +2393,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
             // masks (universe masks read), tables, rows (list masks read, rows written), chunk
             // flags, their prefix and the item list (written, read at the claims), the header
             const uint64_t n1u = (uint64_t)n1, q0 = (uint64_t)nq0;
-            uint64_t b = (!DIAG && nq0 > 256)
-                             ? q0 * (12ull + 16ull * W) + 12ull * (uint64_t)((nq0 + 63) >> 6) + 4ull * (uint64_t)nqk
-                             : 4ull * q0;
+            uint64_t b = drop1 ? 4ull * q0 + 12ull * (uint64_t)((nq0 + 63) >> 6) + 4ull * (uint64_t)nqk +
+                                     (4ull * q0 + 8ull * W * (q0 - (uint64_t)nqk))
+                               : 4ull * q0;
             b += 4ull * (uint64_t)(s0 - nq0) + 20ull * (uint64_t)P1;
-            b += n1u * (24ull + 16ull * W) + 16ull * BITS;
-            b += 8ull * n1u * (uint64_t)qd + 8ull * (uint64_t)d * (uint64_t)v1.nw;
+            b += n1u * (4ull + 8ull * W) + (uint64_t)P1 * (12ull + 8ull * W) + 16ull * BITS;
+            b += (4ull + 8ull) * n1u * (uint64_t)qd + 8ull * (uint64_t)d * (uint64_t)v1.nw;
             b += 24ull * (uint64_t)nch + 8ull * (uint64_t)H + sizeof(FrameState);
             acc.dbytes += b;
         }
@@ -2225,16 +2450,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
         bool src_top = !thief3;  // the current source: top-level items (else one published list)
         // idle workgroups of this launch, as read at the previous check (the load is issued
         // one check ahead, so its latency hides under the chunk in between)
-        uint32_t hungry_seen = 0u;
+        uint32_t hungry_seen = 0u, flags_seen = 0u;
         for (;;) {
             if (!src_top && !find_shared_list(a, sh, me, busyw, idlew, npub, my_slot, nw, thief3)) break;
             FrameState cur = uni_frame(sh->topf);
             int depth = 0;
             while (!aborted) {
-                const FrameView v = frame_view(frame_base(c, cur.off), cur.n, cur.wf, cur.rbits);
+                const FrameView v = frame_view(frame_base(c, cur.off), cur.n, cur.nq, cur.wf, DIAG || cur.off == kShared);
                 int i;
                 if (depth == 0) {
                     if (src_top) {
+                        // a capacity that ran out elsewhere, as read at the previous claim
+                        if (uni(flags_seen) & FLAG_RERUN) {
+                            aborted = true;
+                            break;
+                        }
+                        flags_seen = __hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         int got = 0, mv = 0;
                         if (ln == 0) {
                             if (gclaim) {
@@ -2357,10 +2588,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
                             continue;
                         }
                         cur.chunk = base;
-                        const uint64_t tl = DIAG ? clock64() : 0ull;
                         cur.heavy = (cur.wf == 1) ? light_chunk<1, DIAG, ENUM, TB>(c, cur, v, base, acc)
                                                   : light_chunk<W, DIAG, ENUM, TB>(c, cur, v, base, acc);
-                        if (DIAG) acc.ph[PH_LIGHT] += clock64() - tl;
                         continue;
                     }
                     const int lane = __ffsll((unsigned long long)cur.heavy) - 1;
@@ -2369,9 +2598,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
                 }
                 FrameState ch;
                 const bool report = src_top || depth > 0;
-                const bool pushed = (cur.wf == 1) ? heavy_node<1, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report)
-                                                  : heavy_node<W, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report);
-                if (pushed) {
+                const Node node = (cur.wf == 1) ? heavy_node<1, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report)
+                                                : heavy_node<W, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report);
+                if (node == Node::kPushed) {
                     if (depth >= a.dims.maxdepth) {
                         if (ln == 0) atomicOr(a.flags, (unsigned int)FLAG_DEPTH_OVERFLOW);
                         aborted = true;
@@ -2384,7 +2613,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 ? 4 
                     }
                     ++depth;
                     cur = ch;
-                } else if (__hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & FLAG_STACK_OVERFLOW) {
+                } else if (node == Node::kFull) {
                     aborted = true;
                 }
             }
@@ -2568,8 +2797,7 @@ __device__ __forceinline__ void wide_table_add(const WFrameView &v2, int q, uint
 }
 
 // The candidate at position i of frame F, |R'| >= 2, handled by the whole wave (maximality
-// check, expansion, report, child list).  Returns true when a child frame was written (its
-// state in C).
+// check, expansion, report, child list).
 // IMB: the candidate pruning of section II-C.  Candidates of a list are sorted by count, so an
 // earlier candidate holding all of a candidate's mask has the same mask (a twin).  When x is
 // maximal, its later twins leave the list and join Q with x: a twin whose first twin (the
@@ -2583,7 +2811,7 @@ __device__ __forceinline__ void wide_table_add(const WFrameView &v2, int q, uint
 // covered ones are never taken: they are candidates for p's node and Q entries (positions
 // before) for the nodes after them.
 template <bool DIAG, bool ENUM, bool TB, bool IMB = false, bool PIV = false>
-__device__ __forceinline__ bool heavy_wide(const WCtx &w, const FrameState &F, const WFrameView &v, int i, FrameState &C,
+__device__ __forceinline__ Node heavy_wide(const WCtx &w, const FrameState &F, const WFrameView &v, int i, FrameState &C,
                                            WaveAcc &acc) {
     const Ctx &c = w.c;
     const int ln = lane_id();
@@ -2643,7 +2871,7 @@ __device__ __forceinline__ bool heavy_wide(const WCtx &w, const FrameState &F, c
         }
         if (IMB) gone = !__ballot(inq) && __ballot(inp);
     }
-    if (gone) return false;  // left the list with its first twin: not a node
+    if (gone) return Node::kLeaf;  // left the list with its first twin: not a node
     uint64_t dx = 0, rs = 0;
     if (DIAG) {
         dx = deg_of(c, v.ids[i]);
@@ -2661,7 +2889,7 @@ __device__ __forceinline__ bool heavy_wide(const WCtx &w, const FrameState &F, c
             const uint64_t fw = F.fw - (2ull + dx);
             acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.n - 1) + (uint64_t)r);
         }
-        return false;
+        return Node::kLeaf;
     }
 
     // maximal: per word of positions the OR of R''s rows lists the entries meeting R', the AND
@@ -2825,7 +3053,7 @@ __device__ __forceinline__ bool heavy_wide(const WCtx &w, const FrameState &F, c
         acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.n - 1) + (uint64_t)r + (uint64_t)pn +
                              (uint64_t)qn);
     }
-    if (pn == 0) return false;
+    if (pn == 0) return Node::kLeaf;
 
     // child list: Q' in list order, then P' stably sorted by count; masks compressed to the r
     // bits of R' (child bit t = frame bit bl[t]), mapped to N(x) through orig
@@ -2834,7 +3062,7 @@ __device__ __forceinline__ bool heavy_wide(const WCtx &w, const FrameState &F, c
     const uint64_t top2 = ((uint64_t)off2 + wframe_words(n2, r) + 1ull) & ~1ull;
     if ((int64_t)top2 > c.scap) {
         if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_STACK_OVERFLOW);
-        return false;
+        return Node::kFull;
     }
     uint32_t *cb = c.stk + off2;
     const WFrameView v2 = wframe_view(cb, n2, r);
@@ -3001,7 +3229,7 @@ __device__ __forceinline__ bool heavy_wide(const WCtx &w, const FrameState &F, c
     C.heavy = 0ull;
     C.sL = sL;
     C.fw = DIAG ? wave_sum_u64(fwc) : 0ull;
-    return true;
+    return Node::kPushed;
 }
 
 // Stable counting sort by key, as wave_sort_by_key, with the histogram in global memory.
@@ -3470,7 +3698,8 @@ __global__ __launch_bounds__(512) void wide_kernel(SearchArgs a, int64_t lo, int
                 const int lane = __ffsll((unsigned long long)cur.heavy) - 1;
                 cur.heavy &= cur.heavy - 1ull;
                 FrameState ch;
-                if (heavy_wide<DIAG, ENUM, TB, IMB, PIV>(w, cur, v, cur.chunk + lane, ch, acc)) {
+                const Node node = heavy_wide<DIAG, ENUM, TB, IMB, PIV>(w, cur, v, cur.chunk + lane, ch, acc);
+                if (node == Node::kPushed) {
                     if (depth + 1 >= L.maxdepth) {
                         if (ln == 0) atomicOr(a.flags, (unsigned int)FLAG_DEPTH_OVERFLOW);
                         aborted = true;
@@ -3481,7 +3710,7 @@ __global__ __launch_bounds__(512) void wide_kernel(SearchArgs a, int64_t lo, int
                     if (TB && ln == 0) acc.dbytes += 2ull * sizeof(FrameState);
                     ++depth;
                     cur = ch;
-                } else if (__hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & FLAG_STACK_OVERFLOW) {
+                } else if (node == Node::kFull) {
                     aborted = true;
                 }
             }
