@@ -102,7 +102,7 @@ typedef struct mbe_graph {
  *            stores and atomics request (the design's traffic model, before any cache): the
  *            top-level candidates' reverse scans and local universes, every frame's lists,
  *            per-bit tables and position rows written and read, per node the rows, masks and
- *            tables it reads; the rebuilds of shared lists by helping workgroups are left out,
+ *            tables it reads; the rebuilds of third-level lists by helping waves are left out,
  *            so the tally depends on the graph alone, not on the launch shape or timing
  */
 typedef struct mbe_result {
@@ -138,9 +138,9 @@ typedef struct mbe_result {
  *   steal_k      work sharing below a top-level candidate (the k of section III-D): 2
  *                (default): the candidates of its child list that need a full node are
  *                claimed one at a time by the owning workgroup's waves and, once a workgroup
- *                of the launch is idle (the rest of the list then moves to a global slot), by
- *                idle workgroups, which rebuild the same list; 1: by the owning workgroup
- *                only; 3: as 2, and in the classes of degree above 64 the child lists of
+ *                of the launch is idle (the rest of a list that has been searched for a while
+ *                then moves to a global slot), by idle workgroups, which read the list where it
+ *                was built; 1: by the owning workgroup only; 3: as 2, and in the classes of degree above 64 the child lists of
  *                second-level nodes are shared too: a wave publishes the rest of such a list
  *                (in 64-candidate chunks) once a wave or workgroup is idle, and idle waves of
  *                its workgroup and idle workgroups (after every launch's top-level

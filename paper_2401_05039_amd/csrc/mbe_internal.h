@@ -77,6 +77,7 @@ struct ArenaLayout {
     size_t off_hb;      // u64[ucap/64+1]       top-level candidates with |R'| >= 2, per chunk
     size_t off_hpre;    // u32[ucap/64+2]       popcount prefix of those words
     size_t off_hpos;    // u32[ucap]            their positions, in list order
+    size_t off_top;     // the list's frame state and sizes, for workgroups that share it
     size_t s1_words;
     size_t off_waves;   // start of the per-wave regions
     size_t wave_bytes;  // stride between waves
@@ -130,12 +131,18 @@ struct GraphDesc {
     int32_t pad;
 };
 
-// Work-stealing slot of one workgroup: while it searches a top-level candidate whose child
-// list has more than one 64-candidate chunk left, word = (epoch << 32) | chunks claimed so
-// far (in candidates) and the other fields name the task; word = 0 otherwise.
+// Work-stealing slot of one workgroup (arena slot): once a workgroup of the launch is idle, the
+// owner of a top-level list moves the rest of its items here, word = (epoch << 32) | next item
+// and the other fields name the task; word = 0 otherwise.  Others read the list where its owner
+// built it: readers counts the workgroups that work from this arena slot's list, and the owner
+// keeps the slot until it is zero.  (A list is moved out only when the launch has no top-level
+// candidate left to claim, so its owner never needs the memory for another one.)  A reader
+// counts itself first and then looks at the word again; the owner withdraws the word first and
+// then looks at the count.
 struct StealSlot {
     unsigned long long word;
-    int32_t g, k, limit, pad;
+    int32_t g, k, limit;
+    unsigned int readers;
     unsigned long long pad2;
 };
 
@@ -143,12 +150,13 @@ struct StealSlot {
 // of a second-level node and others are idle, word = (epoch << 32) | 64-candidate chunks of
 // that list claimed so far, and the other fields name the list: graph g, top-level rank k,
 // limit = number of chunks, position i1 of the second-level node in the top-level list, first
-// = list position of chunk 0.  word = 0 otherwise.  Epochs come from a per-launch counter, so
-// a claim against a withdrawn list always fails.  word, g, k and limit sit where they sit in a
-// StealSlot, and the two have the same size: idle workgroups scan both kinds with one loop.
+// = list position of chunk 0, root = the arena slot that holds the top-level list.  word = 0
+// otherwise.  Epochs come from a per-launch counter, so a claim against a withdrawn list always
+// fails.  word, g, k and limit sit where they sit in a StealSlot, and the two have the same
+// size: idle workgroups scan both kinds with one loop.
 struct PubSlot {
     unsigned long long word;
-    int32_t g, k, limit, i1, first, pad;
+    int32_t g, k, limit, i1, first, root;
 };
 static_assert(sizeof(PubSlot) == sizeof(StealSlot), "slot kinds share a stride");
 static_assert(offsetof(PubSlot, limit) == offsetof(StealSlot, limit), "slot kinds share a head");

@@ -57,6 +57,15 @@ namespace {
 
 constexpr uint64_t kHashK = 0x9E3779B97F4A7C15ull;
 constexpr uint32_t kShared = 0xFFFFFFFFu;
+// Ticks of the 100 MHz wall clock.  A top-level list is moved out for others only after its
+// workgroup has searched it for 0.3 ms: from then on every claim is an add on one address for all,
+// and the others read the list through their own L2 (a die has its own), so lists of short items
+// are searched sooner by the eight waves that have them at hand.  A graph of 788 x 540 vertices
+// with 19,000 edges takes 1.0 ms when lists move after 60 us, 0.53 ms after 0.3 ms and 0.44 ms
+// when none moves; the skewed slice (items of milliseconds) takes 1,470 ms without and the same
+// 50 ms with either.
+constexpr uint32_t kShareAfter = 30000;
+constexpr uint32_t kLongItem = 10000;  // an item of 0.1 ms or more is claimed by itself
 constexpr uint32_t kMovedMark = 1u << 30;  // added to the LDS item counter when the list moves  // frame offset meaning "the workgroup's top-level list"
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr int kQKeep = 256;      // most incomparable Q' masks a compressed child keeps
@@ -174,6 +183,13 @@ __device__ __forceinline__ uint32_t align2(uint32_t x) { return (x + 1u) & ~1u; 
 // Wait until this wave's memory operations are done, so that plain stores made by some
 // lanes are in place before other lanes load them.
 __device__ __forceinline__ void wait_mem() { __builtin_amdgcn_s_waitcnt(0); }
+
+// The same where only some lanes come by, and for the compiler too: what follows is read after
+// what precedes has arrived.
+__device__ __forceinline__ void wait_loads() {
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
 
 __device__ __forceinline__ void see_atomics() {
     __builtin_amdgcn_s_waitcnt(0);
@@ -1492,9 +1508,20 @@ struct WGShared {
     int others_done;     // (wave 0) the other launches' top-level candidates are all handed out
     int vpub;            // mode 3: the third-level slot taken, and its epoch
     unsigned int vepoch;
+    int vroot;           // modes 2 and 3: the arena slot that holds the top-level list
+    uint32_t t0;         // wall clock when the search of the current list began
+    int H;               // top-level items, and entries of the local universe, of the current task
+    int us0;
     int tg, tk;          // graph and top-level rank of the current task
     FrameState topf;     // the top-level frame of the current task
     WaveShare ws[16];
+};
+
+// What a workgroup needs of a top-level list that another one built (the rest of it is read in
+// place, in the builder's arena slot).
+struct TopRec {
+    FrameState top;
+    int32_t H, s0;
 };
 
 // Add the workgroup's tallies to a graph's accumulators and clear them.  All threads call.
@@ -1537,6 +1564,14 @@ __device__ __forceinline__ void flush_acc(WaveAcc &acc, unsigned long long *gacc
     }
     __syncthreads();
     acc = WaveAcc{};
+}
+
+// Claim the next n items of a top-level list moved to its steal slot: the first one's index, or
+// limit once the list is used up or withdrawn.  One add: hundreds of waves may claim from one
+// list, and a failed claim does no harm to a counter that only this list ever uses.
+__device__ __forceinline__ int claim_items(unsigned long long *word, unsigned int epoch, int limit, int n) {
+    const unsigned long long old = atomicAdd(word, (unsigned long long)n);
+    return (unsigned int)(old >> 32) == epoch && (unsigned int)old < (unsigned int)limit ? (int)(unsigned int)old : limit;
 }
 
 // Claim the next step items of a published list: returns the first one's index, or -1 once
@@ -1599,7 +1634,7 @@ __device__ __forceinline__ void move_top_list(const SearchArgs &a, WGShared *sh,
         slot->k = k;
         slot->limit = H;
         __threadfence();
-        __hip_atomic_store(&slot->word, ((unsigned long long)epoch << 32) | rest, __ATOMIC_RELEASE,
+        __hip_atomic_store(&slot->word, ((unsigned long long)epoch << 32) | rest, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
         atomicAdd(a.steal_live, 1u);
         sh->published = 1;
@@ -1635,14 +1670,15 @@ __device__ __forceinline__ bool find_shared_list(const SearchArgs &a, WGShared *
         int lim = 0, fi = 0, it = 0;
         if (idx >= 0) {
             PubSlot *ps = &a.pub[idx];
-            const unsigned long long w1 = __hip_atomic_load(&ps->word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long w1 = __hip_atomic_load(&ps->word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             e = (unsigned int)(w1 >> 32);
             if (e != 0u && (ln != 0 || e == sh->vepoch)) {
+                wait_loads();
                 lim = __hip_atomic_load(&ps->limit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 fi = __hip_atomic_load(&ps->first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 it = __hip_atomic_load(&ps->i1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                const unsigned long long w2 = __hip_atomic_load(&ps->word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+                wait_loads();
+                const unsigned long long w2 = __hip_atomic_load(&ps->word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 ok = (unsigned int)(w2 >> 32) == e && (int)(unsigned int)w2 < lim;
             }
         }
@@ -1729,14 +1765,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
     uint32_t *hpos = reinterpret_cast<uint32_t *>(wg + a.lay.off_hpos);
     char *wv = wg + a.lay.off_waves + (size_t)wid * a.lay.wave_bytes;
     FrameState *hdr = reinterpret_cast<FrameState *>(wv + a.lay.off_w_hdr);
+    const uint32_t *hposr = hpos;  // the current task's top-level items
 
     Ctx c;
-    c.gid = gid;
-    c.M = M;
-    c.hvl = hvl;
-    c.degl = degl;
     c.c_off = a.c_off;
-    c.s1 = s1;
     c.stk = reinterpret_cast<uint32_t *>(wv + a.lay.off_w_stack);
     c.stu = reinterpret_cast<uint32_t *>(wv + a.lay.off_w_u);
     c.hist = lds_at<lds_u32>(lds_raw, sizeof(WGShared) + (size_t)wid * BITS * 4);
@@ -1838,7 +1870,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                 }
                 // a published top-level list with at least two unclaimed items, else (third-level
                 // sharing) a published third-level list with at least two unclaimed chunks; 64
-                // slots at a time (the two slot kinds share their head fields and stride)
+                // slots at a time (the two slot kinds share their head fields and stride).  Looking
+                // around is done with relaxed loads, each at the coherent level by itself: an
+                // acquire drops the caches of the whole compute unit and part of its L2 under the
+                // workgroups still at work, again and again.  What is read is checked by the
+                // word, before and after, and the one acquire comes with a task.
                 bool found = false;
 #pragma unroll 1
                 for (int kind = 0; kind < 2 && !found; ++kind) {
@@ -1854,21 +1890,25 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                     for (int base = 1 - kind; base < total && !found; base += 64) {  // (not its own slot)
                         const int j = base + ln;
                         bool ok = false;
-                        int idx = 0, sg = 0, sk = 0;
+                        int idx = 0, sg = 0, sk = 0, rs = 0;
                         unsigned int e = 0;
                         if (j < total) {
                             idx = (start + j) % total;
                             StealSlot *sl = reinterpret_cast<StealSlot *>(arr + (size_t)idx * sizeof(StealSlot));
                             const unsigned long long w1 =
-                                __hip_atomic_load(&sl->word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+                                __hip_atomic_load(&sl->word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                             e = (unsigned int)(w1 >> 32);
                             if (e != 0u) {
+                                wait_loads();
                                 sg = __hip_atomic_load(&sl->g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                                 sk = __hip_atomic_load(&sl->k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                                 const int lim = __hip_atomic_load(&sl->limit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                                rs = kind == 0 ? idx
+                                               : __hip_atomic_load(&reinterpret_cast<PubSlot *>(sl)->root, __ATOMIC_RELAXED,
+                                                                   __HIP_MEMORY_SCOPE_AGENT);
+                                wait_loads();
                                 const unsigned long long w2 =
-                                    __hip_atomic_load(&sl->word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+                                    __hip_atomic_load(&sl->word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                                 // the owner has not moved on, and two or more are left
                                 ok = (unsigned int)(w2 >> 32) == e && (int)(unsigned int)w2 + 2 <= lim;
                             }
@@ -1879,9 +1919,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                             idx = __builtin_amdgcn_readlane(idx, src);
                             sg = __builtin_amdgcn_readlane(sg, src);
                             sk = __builtin_amdgcn_readlane(sk, src);
+                            rs = __builtin_amdgcn_readlane(rs, src);
                             e = (unsigned int)__builtin_amdgcn_readlane((int)e, src);
+                            // counted as a reader of the list's memory first; then the slot has to
+                            // hold the same list still
+                            int held = 0;
+                            if (ln == 0) {
+                                StealSlot *sl = reinterpret_cast<StealSlot *>(arr + (size_t)idx * sizeof(StealSlot));
+                                atomicAdd(&a.steal[rs].readers, 1u);
+                                wait_loads();
+                                const unsigned long long w3 =
+                                    __hip_atomic_load(&sl->word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                held = (unsigned int)(w3 >> 32) == e;
+                                if (!held) atomicSub(&a.steal[rs].readers, 1u);
+                            }
+                            if (!__builtin_amdgcn_readlane(held, 0)) continue;
                             if (ln == 0) {
                                 sh->mode = 2 + kind;
+                                sh->vroot = rs;
                                 sh->victim = idx;
                                 sh->vpub = idx;
                                 sh->epoch = e;
@@ -1964,6 +2019,38 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         const int32_t *row = a.c_adj + rb;
         c.row = row;
         c.x_root = x;
+        // the top-level list and what belongs to it: in this workgroup's arena slot, or where
+        // the list's owner built it
+        const int root_slot = thief ? uni(sh->vroot) : my_slot;
+        {
+            char *rw = a.arena + (size_t)root_slot * a.lay.wg_bytes;
+            c.gid = reinterpret_cast<int32_t *>(rw + a.lay.off_gid);
+            c.M = reinterpret_cast<uint64_t *>(rw + a.lay.off_M);
+            c.hvl = reinterpret_cast<uint64_t *>(rw + a.lay.off_hv);
+            c.degl = reinterpret_cast<uint32_t *>(rw + a.lay.off_deg);
+            c.s1 = reinterpret_cast<uint32_t *>(rw + a.lay.off_S1);
+            hposr = reinterpret_cast<uint32_t *>(rw + a.lay.off_hpos);
+        }
+        TopRec *const rec = reinterpret_cast<TopRec *>(a.arena + (size_t)root_slot * a.lay.wg_bytes + a.lay.off_top);
+        if (thief) {
+            // (building the list anew cost a workgroup 0.1 to 1.2 ms, about half of all the search
+            // time on a graph of 784 x 653 vertices and 40,000 edges and a ninth on the power-law
+            // graph of 10^6 edges: 21.0 -> 19.5 ms there, the skewed slice 68 -> 51 ms)
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (tid == 0) {
+                sh->topf = rec->top;
+                sh->H = rec->H;
+                sh->us0 = rec->s0;
+                sh->claim = 0u;
+                sh->moved = 0u;
+                sh->published = 0;
+                sh->gclaim = mode == 2 ? 1 : 0;
+                sh->tg = g;
+                sh->tk = (int)k;
+                sh->busyw = thief3 ? 0u : (uint32_t)nw;
+                sh->idlew = 0u;
+            }
+        } else {
 
         // -- the 2-hop walk of x, spread over the whole workgroup: walk index t belongs to the
         //    neighbour w_j with woff[j] <= t < woff[j+1] and reads entry wbase[j] + t - woff[j]
@@ -2182,7 +2269,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         __syncthreads();
         const bool root_nonmax = uni(sh->nonmax) != 0;
         const int P1 = uni(sh->pcount);
-        if (TB && tid == 0 && !thief) {
+        if (TB && tid == 0) {
             // x's row; its neighbours' offsets (walk set-up, hash and degree terms); both reverse
             // scans (rows, ranks and mask atomics; bitmap atomics and the universe index lookups
             // unless the bitmap is in LDS); the terms per position of N(x); bitmap prefix,
@@ -2192,7 +2279,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
             acc.dbytes += 4ull * (dd + 2ull) + 16ull * dd + (rl ? 24ull : 44ull) * wk + 12ull * BITS +
                           (rl ? 0ull : 32ull * (uint64_t)nwords) + 8ull * su + 16ull * W * su + 8ull * su;
         }
-        if (tid == 0 && !thief) {  // a stolen task's top-level node belongs to its owner
+        if (tid == 0) {
             const uint64_t dx = (uint64_t)d;
             if (DIAG) {
                 acc.nodes += 1;
@@ -2212,7 +2299,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                 acc.out_ints += 2ull + (uint64_t)nL + (uint64_t)d;
             }
         }
-        if (ENUM && !root_nonmax && !thief && wid == 0) {
+        if (ENUM && !root_nonmax && wid == 0) {
             uint64_t R1[16];
             for (int w = 0; w < 16; ++w) {
                 const int bits = d - 64 * w;
@@ -2349,9 +2436,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         __syncthreads();
 
         // -- top-level light pass: chunks of P1 are split over the waves; candidates with
-        //    |R'| = 1 are settled here (by the owner only), and those with |R'| >= 2 are
-        //    flagged per chunk.  Their ordered list hpos depends on the list alone, so a
-        //    thief that rebuilt the list finds the same items at the same indices.
+        //    |R'| = 1 are settled here, and those to be handled one by one are flagged per chunk
+        //    and listed in order in hpos.
         FrameState top;
         top.off = kShared;
         top.top = 0;
@@ -2368,9 +2454,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         top.fw = uni((uint64_t)sh->fw1);
         top.nm = nq0 + P1;
         top.pad = 0;
-        const int nch = thief3 ? 0 : (P1 + 63) >> 6;  // a third-level thief takes no top-level item
+        const int nch = (P1 + 63) >> 6;
         for (int q = wid; q < nch; q += nw) {
-            const uint64_t hm = light_chunk<W, DIAG, ENUM, TB>(c, top, v1, nqk + 64 * q, acc, !thief);
+            const uint64_t hm = light_chunk<W, DIAG, ENUM, TB>(c, top, v1, nqk + 64 * q, acc);
             if (ln == 0) hb[q] = hm;
         }
         wait_mem();
@@ -2388,7 +2474,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         wait_mem();
         __syncthreads();
         const int H = uni(sh->s0);
-        if (TB && tid == 0 && !thief) {
+        if (TB && tid == 0) {
             // the top-level list: Q1 (pruned, or copied), P1 staged and sorted, ids / hash terms /
             // masks (universe masks read), tables, rows (list masks read, rows written), chunk
             // flags, their prefix and the item list (written, read at the claims), the header
@@ -2403,20 +2489,31 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
             acc.dbytes += b;
         }
 
-        // -- share the items.  The owner's waves claim them from an LDS counter; once a
-        //    workgroup of the launch is idle, the wave whose claim notices it moves the rest of
-        //    the list to the global steal slot, and from then on everyone (idle workgroups
-        //    rebuild the same list) claims there.  A thief claims there from the start.
-        StealSlot *slot = mode == 2 ? &a.steal[sh->victim] : &a.steal[my_slot];
         if (tid == 0) {
             sh->topf = top;
+            sh->t0 = (uint32_t)wall_clock64();
+            sh->H = H;
+            sh->us0 = s0;
             sh->tg = g;
             sh->tk = (int)k;
-            sh->busyw = thief3 ? 0u : (uint32_t)nw;
+            sh->busyw = (uint32_t)nw;
             sh->idlew = 0u;
-            if (mode == 2) sh->gclaim = 1;
+            rec->top = top;
+            rec->H = H;
+            rec->s0 = s0;
         }
+        }  // (own task)
+
+        // -- share the items.  The owner's waves claim them from an LDS counter; once a
+        //    workgroup of the launch is idle, the wave whose claim notices it moves the rest of
+        //    the list to the global steal slot, and from then on everyone (idle workgroups read
+        //    the list in place) claims there.  A thief claims there from the start.
+        StealSlot *slot = mode == 2 ? &a.steal[sh->victim] : &a.steal[my_slot];
+        wait_mem();
         __syncthreads();
+        const FrameState top = uni_frame(sh->topf);
+        const int H = uni(sh->H);
+        c.s0 = uni(sh->us0);
         bool gclaim = uni(sh->gclaim) != 0;
         lds_u32 *claim_l = lds_at<lds_u32>(lds_raw, offsetof(WGShared, claim));
         lds_u32 *moved_l = lds_at<lds_u32>(lds_raw, offsetof(WGShared, moved));
@@ -2451,6 +2548,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         // idle workgroups of this launch, as read at the previous check (the load is issued
         // one check ahead, so its latency hides under the chunk in between)
         uint32_t hungry_seen = 0u, flags_seen = 0u;
+        int inext = 0, iend = 0;  // top-level items claimed and not yet begun
+        uint32_t tclaim = 0u;     // (lane 0) when, and how many, it last claimed from a moved list
+        int sclaim = 1;
         for (;;) {
             if (!src_top && !find_shared_list(a, sh, me, busyw, idlew, npub, my_slot, nw, thief3)) break;
             FrameState cur = uni_frame(sh->topf);
@@ -2466,10 +2566,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                             break;
                         }
                         flags_seen = __hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        int got = 0, mv = 0;
-                        if (ln == 0) {
+                        const bool want = uni(hungry_seen) > 0u;
+                        hungry_seen = __hip_atomic_load(a.hungry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        int got = 0, mv = 0, step = 1;
+                        if (inext < iend) {
+                            got = inext;
+                            step = iend - inext;
+                        } else if (ln == 0) {
                             if (gclaim) {
-                                got = claim_chunk(&slot->word, epoch, H, 1u);
+                                // the counter is one address for every wave of the device: short
+                                // items (by the time the last ones took) are claimed four or eight
+                                // at once while many are left, long ones one by one
+                                const uint32_t now = (uint32_t)wall_clock64();
+                                const uint32_t per = iend > 0 ? (now - tclaim) / (uint32_t)sclaim : kLongItem;
+                                step = per >= kLongItem ? 1 : max(1, min(per >= kLongItem / 4 ? 4 : 8, (H - iend) >> 6));
+                                got = claim_items(&slot->word, epoch, H, step);
+                                tclaim = now;
+                                sclaim = step;
                             } else {
                                 const uint32_t t = lds_add32(claim_l, 1u);
                                 got = (int)(t & (kMovedMark - 1u));
@@ -2478,11 +2591,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                                     // is out (the moving wave is a few stores from done), claim there
                                     while (__hip_atomic_load(moved_l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 1u)
                                         __builtin_amdgcn_s_sleep(1);
-                                    got = claim_chunk(&slot->word, epoch, H, 1u);
+                                    got = claim_items(&slot->word, epoch, H, 1);
                                     mv = 1;
                                 } else if (uint32_t none = 0u;
-                                           a.steal_on && got + 2 < H && (got & 7) == 0 &&
-                                           __hip_atomic_load(a.hungry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0u &&
+                                           a.steal_on && want && got + 2 < H &&
+                                           (uint32_t)wall_clock64() - sh->t0 > kShareAfter &&
                                            __hip_atomic_compare_exchange_strong(moved_l, &none, 2u, __ATOMIC_RELAXED,
                                                                                __ATOMIC_RELAXED,
                                                                                __HIP_MEMORY_SCOPE_WORKGROUP)) {
@@ -2496,7 +2609,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                         got = __builtin_amdgcn_readlane(got, 0);
                         if (__builtin_amdgcn_readlane(mv, 0)) gclaim = true;
                         if (got < 0 || got >= H) break;
-                        i = (int)uni(hpos[got]);
+                        inext = got + 1;
+                        iend = min(H, got + __builtin_amdgcn_readlane(step, 0));
+                        i = (int)uni(hposr[got]);
                         if (k3) me->item1 = i;
                     } else {
                         // a helped list: rebuild it once (the node call below reports nothing)
@@ -2524,7 +2639,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                                     // every chunk is claimed: the owner withdraws the list
                                     base = cur.n;
                                     if (ln == 0 && me->cown) {
-                                        __hip_atomic_store(&a.pub[me->cidx].word, 0ull, __ATOMIC_RELEASE,
+                                        __hip_atomic_store(&a.pub[me->cidx].word, 0ull, __ATOMIC_RELAXED,
                                                            __HIP_MEMORY_SCOPE_AGENT);
                                         atomicSub(a.pub_live, 1u);
                                         lds_add32(npub, ~0u);
@@ -2538,7 +2653,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                                 // the chunk in between)
                                 const bool want = uni(hungry_seen) > 0u;
                                 hungry_seen = __hip_atomic_load(a.hungry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                if (want) {
+                                if (want && (uint32_t)wall_clock64() - uni(sh->t0) > kShareAfter) {
                                     // the top-level list goes out first (its items are the coarser
                                     // work): the owner's next top-level claim may be far off when
                                     // second-level subtrees are large
@@ -2565,8 +2680,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                                             mp->i1 = me->item1;
                                             mp->first = base;
                                             mp->limit = lim;
+                                            mp->root = root_slot;
                                             __threadfence();
-                                            __hip_atomic_store(&mp->word, (unsigned long long)e << 32, __ATOMIC_RELEASE,
+                                            __hip_atomic_store(&mp->word, (unsigned long long)e << 32, __ATOMIC_RELAXED,
                                                                __HIP_MEMORY_SCOPE_AGENT);
                                             atomicAdd(a.pub_live, 1u);
                                             lds_add32(npub, 1u);
@@ -2623,7 +2739,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                 atomicOr(a.flags, (unsigned int)FLAG_SHARE_MISMATCH);
             // (after an abort) a list still published is withdrawn
             if (ln == 0 && me->cown) {
-                __hip_atomic_store(&a.pub[me->cidx].word, 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&a.pub[me->cidx].word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 atomicSub(a.pub_live, 1u);
                 lds_add32(npub, ~0u);
             }
@@ -2639,8 +2755,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         __syncthreads();
         // every chunk is claimed: withdraw the list (thieves still finish the chunks they hold)
         if (tid == 0 && sh->published) {
-            __hip_atomic_store(&slot->word, 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            atomicExch(&slot->word, 0ull);
             atomicSub(a.steal_live, 1u);
+        }
+        if (tid == 0 && thief) {
+            wait_loads();
+            atomicSub(&a.steal[root_slot].readers, 1u);
         }
     }
 
@@ -2653,6 +2773,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
             a.wg_load[3 * (size_t)blockIdx.x + 1] = wall_clock64();
             a.wg_load[3 * (size_t)blockIdx.x + 2] = ld_wait;
         }
+        // the arena slot goes back when no workgroup reads this one's last list any more (each
+        // searches what it claimed and leaves; none waits for this one)
+        while (__hip_atomic_load(&a.steal[my_slot].readers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
+            __builtin_amdgcn_s_sleep(32);
         __threadfence();
         atomicExch(&a.slot_busy[my_slot], 0u);
     }
@@ -3883,6 +4007,7 @@ ArenaLayout search_layout(const SearchDims &d) {
     L.off_hb = take((ucap / 64 + 1) * 8);
     L.off_hpre = take((ucap / 64 + 2) * 4);
     L.off_hpos = take(ucap * 4);
+    L.off_top = take(sizeof(TopRec));
     L.off_waves = o;
     size_t w = 0;
     auto wtake = [&](size_t bytes) {
