@@ -444,9 +444,26 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
 
     // record arena for mbe_enumerate
     unsigned long long rec_cap = 0, offs_cap = 0;
+    bool rec_batch = false;
     if (enumerate) {
-        rec_cap = ucap_ints;
-        offs_cap = ucap_ints / 4 + 1;
+        // Waves keep reserves of the arena (see reserve_records) where its ints fit 32 bits and
+        // memory has room.  A wave leaves less than an eighth of the next batch's ints unused when
+        // it takes that one, and at the end holds less than one batch: the largest, or, as batches
+        // double and hold an eighth of what the records between them took, 8 times its ints.
+        unsigned long long nwaves = 0;
+        for (int c = 0; c < 5; ++c)
+            if (std::max(cls_lo[c], lo) < std::min(cls_hi[c], hi))
+                nwaves += (unsigned long long)waves *
+                          (unsigned long long)(grid > 0 ? grid : st->cus * search_occupancy(1 << c, opt.diag, true, waves, dims.nwords));
+        const unsigned long long ints = ucap_ints + ucap_ints / 7 + std::min<unsigned long long>(nwaves * kRecInts * kRecBatchMax, 10 * ucap_ints) +
+                                        nwaves * kRecInts * 12;
+        const unsigned long long ids = ucap_ints / 4 + 1 + std::min<unsigned long long>(nwaves * kRecBatchMax, ucap_ints) + nwaves * 8;
+        if ((ints >> 32) == 0) {
+            rec_batch = st->rec.ensure((size_t)ints * 4 + 256) == hipSuccess && st->rec_offs.ensure((size_t)ids * 8) == hipSuccess;
+            if (!rec_batch) (void)hipGetLastError();
+        }
+        rec_cap = rec_batch ? ints : ucap_ints;
+        offs_cap = rec_batch ? ids : ucap_ints / 4 + 1;
         MBE_TRY(st->rec.ensure((size_t)rec_cap * 4 + 256));
         MBE_TRY(st->rec_offs.ensure((size_t)offs_cap * 8));
     }
@@ -482,6 +499,7 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
     a.rec_cap = rec_cap;
     a.rec_offs = enumerate ? st->rec_offs.as<unsigned long long>() : nullptr;
     a.rec_offs_cap = offs_cap;
+    a.rec_batch = rec_batch ? 1 : 0;
 
     unsigned long long hacc[ACC_SLOTS];
     unsigned int hflags = 0;
@@ -513,14 +531,15 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
 
     if (!enumerate) return MBE_OK;
     if ((hflags & FLAG_RECORD_OVERFLOW) || out->out_ints > ucap_ints) return MBE_ERR_BUFFER_TOO_SMALL;
-    const unsigned long long n_rec = hacc[ACC_RECORDS];
+    const unsigned long long n_rec = out->count;
+    const unsigned long long n_slots = rec_batch ? hacc[ACC_REC_INTS] >> 32 : hacc[ACC_RECORDS];
     if (n_rec == 0) return MBE_OK;
-    MBE_TRY(st->rec_tmp.ensure((size_t)n_rec * 8));
+    MBE_TRY(st->rec_tmp.ensure((size_t)n_slots * 2 * sizeof(RecordKey)));
     MBE_TRY(st->rec_lens.ensure((size_t)n_rec * 8));
     size_t canon_bytes = 0;
-    MBE_TRY(canonical_records(st->rec.as<int32_t>(), st->rec_offs.as<unsigned long long>(), n_rec,
-                              st->rec_tmp.as<unsigned long long>(), st->rec_lens.as<unsigned long long>(), nullptr,
-                              nullptr, &canon_bytes, s));
+    MBE_TRY(canonical_records(st->rec.as<int32_t>(), st->rec_offs.as<unsigned long long>(), n_slots, n_rec,
+                              st->rec_tmp.as<RecordKey>(), st->rec_lens.as<unsigned long long>(), nullptr, nullptr,
+                              &canon_bytes, s));
     MBE_TRY(st->canon_tmp.ensure(canon_bytes));
     canon_bytes = st->canon_tmp.bytes;
     int32_t *dst = ubuf;
@@ -528,9 +547,9 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
         MBE_TRY(st->out_tmp.ensure((size_t)out->out_ints * 4));
         dst = st->out_tmp.as<int32_t>();
     }
-    MBE_TRY(canonical_records(st->rec.as<int32_t>(), st->rec_offs.as<unsigned long long>(), n_rec,
-                              st->rec_tmp.as<unsigned long long>(), st->rec_lens.as<unsigned long long>(), dst,
-                              st->canon_tmp.p, &canon_bytes, s));
+    MBE_TRY(canonical_records(st->rec.as<int32_t>(), st->rec_offs.as<unsigned long long>(), n_slots, n_rec,
+                              st->rec_tmp.as<RecordKey>(), st->rec_lens.as<unsigned long long>(), dst, st->canon_tmp.p,
+                              &canon_bytes, s));
     if (!ubuf_on_device) MBE_TRY(hipMemcpyAsync(ubuf, dst, (size_t)out->out_ints * 4, hipMemcpyDeviceToHost, s));
     MBE_TRY(hipStreamSynchronize(s));
     return MBE_OK;

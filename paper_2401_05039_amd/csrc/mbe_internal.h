@@ -17,14 +17,19 @@ enum AccSlot : int {
     ACC_NONMAX = 4,
     ACC_BYTES = 5,
     ACC_MAX_DEPTH = 6,
-    ACC_RECORDS = 7,    // records reserved in the record arena
-    ACC_REC_INTS = 8,   // ints reserved in the record arena
+    ACC_RECORDS = 7,    // records reserved in the record arena (no reserves kept)
+    ACC_REC_INTS = 8,   // ints reserved in the record arena; with reserves kept, indices << 32 too
     ACC_NEED_UCAP = 9,  // largest universe met (max), for resizing after an overflow
     ACC_SHARED = 10,    // third-level chunks searched by a wave other than the list's owner
     ACC_PHASE = 11,     // 6 slots: shader-clock cycles per search phase (diagnostics only)
     ACC_DBYTES = 17,    // design-byte tally of the production search (tally instances only)
     ACC_SLOTS = 24,
 };
+
+// Reservations of the record arena that waves keep: of kRecBatch0 records at first, doubling up
+// to kRecBatchMax, with kRecInts ints for each.
+constexpr unsigned int kRecBatch0 = 4, kRecBatchMax = 64, kRecInts = 16;
+constexpr unsigned long long kNoRecord = ~0ull;  // an index that holds no record
 
 // Search phases timed in diagnostics mode (cycles summed over waves).
 enum Phase : int {
@@ -213,6 +218,7 @@ struct SearchArgs {
     unsigned long long rec_cap;
     unsigned long long *rec_offs;
     unsigned long long rec_offs_cap;
+    int32_t rec_batch;  // nonzero: the arena has room for the reserves that waves keep
 };
 
 // Arena layout for the given capacities (host side).
@@ -279,8 +285,12 @@ hipError_t sort_pairs_u32_u64(void *temp, size_t *temp_bytes, const unsigned int
                               hipStream_t s);
 
 // Record canonicalisation (mbe_records.hip).
-hipError_t canonical_records(const int32_t *rec, unsigned long long *offs, unsigned long long n_rec,
-                             unsigned long long *offs_tmp, unsigned long long *lens,
+struct RecordKey {
+    unsigned long long head;  // first two vertices of side A
+    unsigned long long off;
+};
+hipError_t canonical_records(int32_t *rec, unsigned long long *offs, unsigned long long n_slots,
+                             unsigned long long n_rec, RecordKey *keys, unsigned long long *lens,
                              int32_t *out, void *temp, size_t *temp_bytes, hipStream_t s);
 
 }  // namespace mbe

@@ -78,7 +78,7 @@ constexpr int kQReduce = 256;
 // candidates, in global scratch for longer ones.
 constexpr int kStuLds = 256;
 static_assert(2 * kStuLds >= 64 * 8, "P' masks of 64 entries fit the second half");
-constexpr int kWaveLds = 1024 + 8 * kQKeep + 4 * kStuLds;  // LDS bytes per wave besides the histogram
+constexpr int kWaveLds = 1024 + 8 * kQKeep + 4 * kStuLds + 32;  // LDS bytes per wave besides the histogram
 // The fixed-width classes keep a graph's rank bitmap and its popcount prefix in LDS, after the
 // waves' regions, when the bitmap has at most this many words (131,072 candidates); larger
 // graphs keep them in the workgroup's arena slot.
@@ -393,7 +393,13 @@ struct Ctx {
     int64_t scap;
     int32_t x_root, s0, c_is_v, Wroot;
     int32_t cbase, obase;  // first packed id of the current graph's candidate / other side
-    // records
+    // records: rows and universe indices of the top-level list, the row words, and the universe
+    // entries that hold all of N(x_root) (they are in no list)
+    const uint64_t *trows;
+    const uint32_t *tids;
+    int tnw, tfull, rec_batch;
+    lds_u64 *res;  // this wave's reserve of the record arena: ints from, index from, left (ints,
+                   // indices << 32), records in the next reservation of each; NULL: none is kept
     int32_t *rec;
     unsigned long long rec_cap, rec_offs_cap;
     unsigned long long *rec_offs;
@@ -478,33 +484,196 @@ __device__ __forceinline__ void wave_sort_by_key(const uint32_t *src, const uint
     }
 }
 
+// Place of n records in the arena: the ints start at off; the first n1 of them have the indices
+// from idx on, the others those from idx2 on.
+struct RecPlace {
+    unsigned long long off, idx, idx2;
+    int n1;
+    __device__ __forceinline__ unsigned long long index(int j) const {
+        return j < n1 ? idx + (unsigned long long)j : idx2 + (unsigned long long)(j - n1);
+    }
+};
+
+// Reserves n records of len ints in all (one wave).  The arena's counters are one address for the
+// whole device, which takes an atomic every 8 to 16 ns: with two per record, listing a power-law
+// graph of 20,000 x 10,000 vertices (516,620 records) took three times its search, 6.5 ms against
+// 2.4 now.  So a wave keeps ints and indices in reserve (c.res, LDS) and asks for 4 to 64
+// records' worth at a time, twice as much each time; records of more than an eighth of that are
+// asked for by themselves.  Both counters share one 64-bit word (indices above bit 32).  Indices a
+// wave has left at the end are marked as holding no record, ints left over are lost; the arena is
+// sized for that.  The wide search, whose nodes
+// cost far more, keeps no reserve; without room for them (c.rec_batch == 0) none is kept.
+__device__ __forceinline__ RecPlace reserve_records(const Ctx &c, unsigned int len, int n) {
+    const int ln = lane_id();
+    RecPlace p;
+    p.n1 = n;
+    p.idx2 = 0;
+    if (!c.res) {
+        unsigned long long o = 0, x = 0;
+        if (ln == 0) {
+            if (c.rec_batch) {
+                x = atomicAdd(&c.acc[ACC_REC_INTS], ((unsigned long long)n << 32) | len);
+                o = x & 0xFFFFFFFFull;
+                x >>= 32;
+            } else {
+                o = atomicAdd(&c.acc[ACC_REC_INTS], (unsigned long long)len);
+                x = atomicAdd(&c.acc[ACC_RECORDS], (unsigned long long)n);
+            }
+        }
+        p.off = readlane64(o, 0);
+        p.idx = readlane64(x, 0);
+        return p;
+    }
+    unsigned long long off = uni((uint64_t)c.res[0]), idx = uni((uint64_t)c.res[1]);
+    const uint64_t st = uni((uint64_t)c.res[2]), gr = uni((uint64_t)c.res[3]);
+    unsigned int left = (unsigned int)st, bi = (unsigned int)gr, bn = (unsigned int)(gr >> 32);
+    int ileft = (int)(st >> 32);
+    const bool more_i = len > left, direct = more_i && 8u * len > kRecInts * bi, more_n = n > ileft;
+    if (more_i || more_n) {
+        const unsigned int ai = !more_i ? 0u : direct ? len : kRecInts * bi;
+        const unsigned int an = more_n ? (unsigned int)(n - ileft) + bn - 1u : 0u;
+        unsigned long long o = 0;
+        if (ln == 0) o = atomicAdd(&c.acc[ACC_REC_INTS], ((unsigned long long)an << 32) | ai);
+        o = readlane64(o, 0);
+        if (more_i && !direct) {
+            off = o & 0xFFFFFFFFull;
+            left = ai;
+        }
+        if (more_i) bi = min(2u * bi, kRecBatchMax);
+        p.off = direct ? o & 0xFFFFFFFFull : off;
+        p.idx = idx;
+        if (more_n) {
+            p.n1 = ileft;
+            p.idx2 = o >> 32;
+            idx = p.idx2 + (unsigned long long)(n - ileft);
+            ileft = (int)bn - 1;
+            bn = min(2u * bn, kRecBatchMax);
+        } else {
+            idx += (unsigned long long)n;
+            ileft -= n;
+        }
+    } else {
+        p.off = off;
+        p.idx = idx;
+        idx += (unsigned long long)n;
+        ileft -= n;
+    }
+    if (!direct) {
+        off += len;
+        left -= len;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (ln == 0) {
+        c.res[0] = off;
+        c.res[1] = idx;
+        c.res[2] = ((uint64_t)(uint32_t)ileft << 32) | left;
+        c.res[3] = ((uint64_t)bn << 32) | bi;
+    }
+    __builtin_amdgcn_wave_barrier();
+    return p;
+}
+
+// Reserve the record of a maximal biclique (one wave): where it goes, or NULL when the record
+// arena is full.  The head is written, and L' / R' go to pl and pr.
+__device__ __forceinline__ int32_t *record_at(const Ctx &c, int nL, int r, int32_t *&pl, int32_t *&pr) {
+    const int ln = lane_id();
+    const unsigned int len = 2u + (unsigned int)nL + (unsigned int)r;
+    const RecPlace p = reserve_records(c, len, 1);
+    if (p.off + len > c.rec_cap || p.index(0) >= c.rec_offs_cap) {
+        if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_RECORD_OVERFLOW);
+        return nullptr;
+    }
+    int32_t *o = c.rec + p.off;
+    pl = o + 2 + (c.c_is_v ? r : 0);   // where L' goes
+    pr = o + 2 + (c.c_is_v ? 0 : nL);  // where R' goes
+    if (ln == 0) {
+        o[0] = c.c_is_v ? r : nL;
+        o[1] = c.c_is_v ? nL : r;
+        c.rec_offs[p.index(0)] = p.off;
+        pl[0] = c.x_root - c.cbase;
+    }
+    return o;
+}
+
+// One 64-word block of an L' as bits of the top-level list, a word per lane: its vertices go to
+// pl[k..), which has room for nL.  Returns k past them.
+__device__ __forceinline__ int write_members(const Ctx &c, uint64_t a, int wd, int32_t *pl, int k, int nL) {
+    const int pc = __popcll(a);
+    const int incl = wave_incl_scan(pc);
+    int at = k + incl - pc;
+    for (; a; a &= a - 1ull, ++at)
+        if (at < nL)  // never past the reserved record
+            pl[at] = c.gid[c.tids[64 * wd + __ffsll((unsigned long long)a) - 1]] - c.cbase;
+    return k + last_lane(incl);
+}
+
+// The record of a maximal node of the fixed mask classes, R' given as r positions of N(x_root) in
+// c.hist: L' = {x_root} u the entries of the top-level list that hold all of R', the AND of its
+// rows, a word per lane, instead of a pass over the universe's masks.  Only where no universe
+// entry holds all of N(x_root) (c.tfull == 0): those are in no list.
+__device__ __forceinline__ void write_record_rows(const Ctx &c, int nL, int r) {
+    const int ln = lane_id();
+    int32_t *pl, *pr;
+    if (!record_at(c, nL, r, pl, pr)) return;
+    int k = 1;
+    for (int base = 0; base < c.tnw; base += 64) {
+        const int wd = base + ln;
+        uint64_t a = wd < c.tnw ? ~0ull : 0ull;
+        for (int t = 0; t < r; t += 4) {
+            uint32_t b[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[q] = uni(c.hist[t + q < r ? t + q : t]);
+            if (wd < c.tnw)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) a &= c.trows[(size_t)b[q] * c.tnw + wd];
+        }
+        k = write_members(c, a, wd, pl, k, nL);
+    }
+    for (int t = ln; t < r; t += 64) pr[t] = c.row[c.hist[t]] - c.obase;
+    __builtin_amdgcn_wave_barrier();  // the next node's bits go to c.hist
+}
+
+// The records of a chunk's maximal nodes of |R'| = 1 (lanes in own; lane l's R' is position rp of
+// N(x_root), its L' has nL vertices), reserved together.  c.tfull == 0 as above.
+__device__ __forceinline__ void write_leaf_records(const Ctx &c, uint64_t own, uint32_t rp, int nL) {
+    const int ln = lane_id();
+    const bool mine = (own >> ln) & 1ull;
+    const int len = mine ? 3 + nL : 0;
+    const int incl = wave_incl_scan(len);
+    const RecPlace p = reserve_records(c, (unsigned int)last_lane(incl), __popcll(own));
+    const unsigned long long off = p.off + (unsigned long long)(unsigned int)(incl - len);
+    const unsigned long long idx = p.index(__popcll(own & lanes_below()));
+    const bool fits = mine && off + (unsigned long long)len <= c.rec_cap && idx < c.rec_offs_cap;
+    if (mine && !fits) atomicOr(c.flags, (unsigned int)FLAG_RECORD_OVERFLOW);
+    if (fits) {
+        int32_t *o = c.rec + off;
+        o[0] = c.c_is_v ? 1 : nL;
+        o[1] = c.c_is_v ? nL : 1;
+        c.rec_offs[idx] = off;
+        o[2 + (c.c_is_v ? 1 : 0)] = c.x_root - c.cbase;
+        o[2 + (c.c_is_v ? 0 : nL)] = c.row[rp] - c.obase;
+    }
+    for (uint64_t q = __ballot(fits); q; q &= q - 1ull) {
+        const int l = __ffsll((unsigned long long)q) - 1;
+        int32_t *pl = c.rec + readlane64(off, l) + 2 + (c.c_is_v ? 1 : 0);
+        const uint64_t *row = c.trows + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)rp, l) * c.tnw;
+        const int n = __builtin_amdgcn_readlane(nL, l);
+        int k = 1;
+        for (int base = 0; base < c.tnw; base += 64) {
+            const int wd = base + ln;
+            k = write_members(c, wd < c.tnw ? row[wd] : 0ull, wd, pl, k, n);
+        }
+    }
+}
+
 // Write the record of the maximal biclique (L', R') of a node.  R' is given as positions of
 // N(x_root) (Rr, Wroot words).  L' = {x_root} u {universe v : M[v] contains R'}: every vertex
 // adjacent to all of R'.  Sides are sorted later by the canonicaliser.
 __device__ __forceinline__ void write_record(const Ctx &c, const uint64_t *Rr, int nL, int r) {
     const int ln = lane_id();
     const uint64_t below = lanes_below();
-    const unsigned long long len = 2ull + (unsigned long long)nL + (unsigned long long)r;
-    unsigned long long off = 0, idx = 0;
-    if (ln == 0) {
-        off = atomicAdd(&c.acc[ACC_REC_INTS], len);
-        idx = atomicAdd(&c.acc[ACC_RECORDS], 1ull);
-    }
-    off = __shfl(off, 0);
-    idx = __shfl(idx, 0);
-    if (off + len > c.rec_cap || idx >= c.rec_offs_cap) {
-        if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_RECORD_OVERFLOW);
-        return;
-    }
-    int32_t *o = c.rec + off;
-    int32_t *pl = o + 2 + (c.c_is_v ? r : 0);   // where L' goes
-    int32_t *pr = o + 2 + (c.c_is_v ? 0 : nL);  // where R' goes
-    if (ln == 0) {
-        o[0] = c.c_is_v ? r : nL;
-        o[1] = c.c_is_v ? nL : r;
-        c.rec_offs[idx] = off;
-        pl[0] = c.x_root - c.cbase;
-    }
+    int32_t *pl, *pr;
+    if (!record_at(c, nL, r, pl, pr)) return;
     int k = 1;
     for (int base = 0; base < c.s0; base += 64) {
         const int li = base + ln;
@@ -612,7 +781,7 @@ __device__ __forceinline__ uint64_t check_chunk(const Ctx &c, const FrameState &
 
 // Candidates [base, base+64) of frame F: lanes with |R'| = 1 are settled here; returned are the
 // lanes still to be handled one by one: |R'| >= 2, and for one-word masks maximal (with records
-// on, maximal candidates of |R'| = 1 too).
+// on and vertices in no list, c.tfull, maximal candidates of |R'| = 1 too).
 template <int WF, bool DIAG, bool ENUM, bool TB = false>
 __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &F, const FrameView &v, int base, WaveAcc &acc,
                                 bool settle = true) {
@@ -628,20 +797,26 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
         r += __popcll(m[w]);
     }
     bool own = false;  // |R'| = 1 and maximal: no earlier entry holds its bit
+    // records of |R'| = 1 are written here, unless vertices outside the lists belong to them
+    const bool here = !ENUM || c.tfull == 0;
+    uint32_t rp = 0;
+    int nL = 0;
     if (act && r == 1) {
         int b = 0;
 #pragma unroll
         for (int w = 0; w < WF; ++w)
             if (m[w]) b = 64 * w + __ffsll((unsigned long long)m[w]) - 1;
         own = v.first[b] == (uint32_t)i + 1u;
-        if (settle && own && !ENUM) {
+        if (settle && own && here) {
             // L' = L u {every entry with bit b}: all of them sit at positions >= i
             const uint64_t sL = F.sL + v.H[b];
             acc.count += 1;
             acc.hash += pair_hash(c.c_is_v, sL, root_hash(c, F, v, (uint32_t)b));
-            acc.out_ints += 2ull + (uint64_t)F.nL + (uint64_t)v.cnt[b] + 1ull;
+            nL = F.nL + (int)v.cnt[b];
+            acc.out_ints += 3ull + (uint64_t)nL;
+            if (ENUM) rp = root_pos(F, v, (uint32_t)b);
         }
-        if (DIAG && settle && !(ENUM && own)) {
+        if (DIAG && settle && (here || !own)) {
             acc.nodes += 1;
             if (!own) acc.nonmax += 1;
             if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
@@ -661,7 +836,11 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
         if (hv) hv &= ~check_chunk<DIAG, TB>(c, F, v, base, m[0], hv, acc, settle);
         if (DIAG) acc.ph[PH_CHECK] += clock64() - t1;
     }
-    if (ENUM) hv |= __ballot(own);
+    if (ENUM) {
+        const uint64_t ob = __ballot(own);
+        if (!here) hv |= ob;
+        else if (settle && ob) write_leaf_records(c, ob, rp, nL);
+    }
     return hv;
 }
 
@@ -1399,19 +1578,35 @@ __device__ __forceinline__ Node heavy_node(const Ctx &c, const FrameState &F, co
         }
     }
     if (ENUM && report) {
-        uint64_t Rr[16];
-        for (int w = 0; w < 16; ++w) Rr[w] = 0ull;
-#pragma unroll
-        for (int w = 0; w < WF; ++w) {
-            uint64_t mm = g.m[w];
-            while (mm) {
-                const int b = 64 * w + __ffsll((unsigned long long)mm) - 1;
-                mm &= mm - 1ull;
-                const uint32_t rp = root_pos(F, v, (uint32_t)b);
-                Rr[rp >> 6] |= 1ull << (rp & 63);
+        if (c.tfull == 0) {
+            // the bits' positions of N(x_root) take the bits' place in c.hist meanwhile
+            __builtin_amdgcn_wave_barrier();
+            if (F.narrow) {
+                const uint32_t bt = ln < r ? c.hist[ln] : 0u;
+                if (ln < r) c.hist[ln] = v.orig[bt];
+                __builtin_amdgcn_wave_barrier();
+                write_record_rows(c, nL, r);
+                __builtin_amdgcn_wave_barrier();
+                if (ln < r) c.hist[ln] = bt;
+                __builtin_amdgcn_wave_barrier();
+            } else {
+                write_record_rows(c, nL, r);
             }
+        } else {
+            uint64_t Rr[16];
+            for (int w = 0; w < 16; ++w) Rr[w] = 0ull;
+#pragma unroll
+            for (int w = 0; w < WF; ++w) {
+                uint64_t mm = g.m[w];
+                while (mm) {
+                    const int b = 64 * w + __ffsll((unsigned long long)mm) - 1;
+                    mm &= mm - 1ull;
+                    const uint32_t rp = root_pos(F, v, (uint32_t)b);
+                    Rr[rp >> 6] |= 1ull << (rp & 63);
+                }
+            }
+            write_record(c, Rr, nL, r);
         }
-        write_record(c, Rr, nL, r);
     }
     if (DIAG && report) {
         dx = deg_of(c, v.ids[i]);
@@ -1768,6 +1963,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
     const uint32_t *hposr = hpos;  // the current task's top-level items
 
     Ctx c;
+    c.res = nullptr;
     c.c_off = a.c_off;
     c.stk = reinterpret_cast<uint32_t *>(wv + a.lay.off_w_stack);
     c.stu = reinterpret_cast<uint32_t *>(wv + a.lay.off_w_u);
@@ -1781,6 +1977,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         c.qk = lds_at<lds_u64>(lds_raw, tb + 1024);
         c.stu_l = reinterpret_cast<uint32_t *>(lds_raw + tb + 1024 + 8 * kQKeep);
         c.pm = lds_at<lds_u64>(lds_raw, tb + 1024 + 8 * kQKeep + 2 * kStuLds);
+        if (ENUM && a.rec_batch) {
+            c.res = lds_at<lds_u64>(lds_raw, tb + 1024 + 8 * kQKeep + 4 * kStuLds);
+            c.res[0] = 0ull;
+            c.res[1] = 0ull;
+            c.res[2] = 0ull;
+            c.res[3] = ((uint64_t)kRecBatch0 << 32) | kRecBatch0;
+        }
     }
     // the rank bitmap and its prefix: in LDS when the launch's graphs are small enough
     const bool rl = a.dims.nwords <= kRankLdsWords;
@@ -1801,6 +2004,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
     c.rec_cap = a.rec_cap;
     c.rec_offs = a.rec_offs;
     c.rec_offs_cap = a.rec_offs_cap;
+    c.rec_batch = a.rec_batch;
     c.acc = a.acc;
     c.flags = a.flags;
 
@@ -2454,6 +2658,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         top.fw = uni((uint64_t)sh->fw1);
         top.nm = nq0 + P1;
         top.pad = 0;
+        if (ENUM) {  // for the records of the top-level light pass
+            c.trows = v1.rows;
+            c.tids = v1.ids;
+            c.tnw = v1.nw;
+            c.tfull = sh->nexp;
+        }
         const int nch = (P1 + 63) >> 6;
         for (int q = wid; q < nch; q += nw) {
             const uint64_t hm = light_chunk<W, DIAG, ENUM, TB>(c, top, v1, nqk + 64 * q, acc);
@@ -2514,6 +2724,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         const FrameState top = uni_frame(sh->topf);
         const int H = uni(sh->H);
         c.s0 = uni(sh->us0);
+        if (ENUM) {
+            const FrameView tv = frame_view(c.s1, top.n, top.nq, W, true);
+            c.trows = tv.rows;
+            c.tids = tv.ids;
+            c.tnw = tv.nw;
+            c.tfull = top.nL - 1;  // (a helper's too: nL counts x_root and the entries in no list)
+        }
         bool gclaim = uni(sh->gclaim) != 0;
         lds_u32 *claim_l = lds_at<lds_u32>(lds_raw, offsetof(WGShared, claim));
         lds_u32 *moved_l = lds_at<lds_u32>(lds_raw, offsetof(WGShared, moved));
@@ -2764,6 +2981,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         }
     }
 
+    if (ENUM && c.res) {  // the indices this wave has left hold no record
+        const unsigned long long idx = c.res[1];
+        const int ileft = (int)((uint64_t)c.res[2] >> 32);
+        if (ln < ileft && idx + (unsigned long long)ln < c.rec_offs_cap) c.rec_offs[idx + (unsigned long long)ln] = kNoRecord;
+    }
     // tallies of the last graph
     if (sh->graph >= 0) flush_acc<DIAG, TB>(acc, a.graphs[sh->graph].acc, sh);
     __syncthreads();
@@ -3445,6 +3667,8 @@ __global__ __launch_bounds__(512) void wide_kernel(SearchArgs a, int64_t lo, int
     c.rec_cap = a.rec_cap;
     c.rec_offs = a.rec_offs;
     c.rec_offs_cap = a.rec_offs_cap;
+    c.rec_batch = a.rec_batch;
+    c.res = nullptr;
     c.acc = a.acc;
     c.flags = a.flags;
     w.stu2 = reinterpret_cast<uint32_t *>(wv + L.off_w_u2);

@@ -70,6 +70,22 @@ def test_workload1_full_list(mbe, orc):
     assert mbe.decode_records(flat) == want["list"]
 
 
+# Records: sides at the edges of their sort (16 lanes with up to 4 entries each, longer sides in
+# memory), records above and below an eighth of the arena ints a wave reserves at a time (64 to
+# 1024), top-level sets held by whole universes (complete blocks) and not, mask classes 1 to 16.
+@pytest.mark.parametrize("nu,nv,p", [(1, 1, 1.0), (16, 17, 1.0), (63, 65, 1.0), (129, 64, 1.0), (300, 1, 1.0),
+                                     (16, 40, 0.5), (9, 300, 0.6), (300, 9, 0.6), (6, 900, 0.6), (60, 60, 0.2)])
+def test_record_paths(mbe, orc, nu, nv, p):
+    g = gg.complete(nu, nv) if p == 1.0 else gg.random_small(nu, nv, p, 43)
+    _say("records", nu, nv, p)
+    for side in (1, 2):
+        want = orc.mbea(g, side=side, want_list=True)
+        for kw in (dict(), dict(steal_k=3, grid=4), dict(diagnostics=True)):
+            res, flat = mbe.mbe_enumerate(g, mbe.Options(side=side, **kw))
+            assert (res["count"], res["hash"], len(flat)) == (want["count"], want["hash"], want["out_ints"]), kw
+            assert mbe.decode_records(flat) == want["list"], kw
+
+
 def test_workload1_golden(mbe):
     gold = json.load(open(os.path.join(GOLDEN, "workloads.json")))["config1"]
     _say("workload1 golden")
