@@ -163,8 +163,11 @@ typedef struct mbe_result {
  *                   candidates whose neighbours within R are all neighbours of p (every
  *                   maximal biclique holding one of them holds p) are never taken: they are
  *                   candidates for p's node and Q entries for the nodes after them.
- *                Either way every top-level candidate is searched by the wide search, Q
- *                lists are kept whole, and the fixed mask classes are not used.  Other
+ *                With diagnostics 1, on a workspace and in mbe_count_noalloc every top-level
+ *                candidate is searched by the wide search, Q lists are kept whole, and the
+ *                fixed mask classes are not used.  Elsewhere, where no tally shows the tree,
+ *                only candidates of degree above 1024 are searched so, and the mask classes
+ *                search theirs without the pruning, which is faster.  Other
  *                values, and pruning with diagnostics = 2, mbe_count_loads or the batched
  *                and served forms: MBE_ERR_INVALID_ARG.
  *   workspace, workspace_bytes

@@ -787,6 +787,21 @@ def test_prune_records(mbe, orc):
     assert mbe.decode_records(flat) == want["list"]
 
 
+# Pruned calls without tallies are searched by mask class, those on fixed memory and with tallies by
+# the pruned wide search: the answers are the same.
+@pytest.mark.parametrize("prune", [1, 2])
+@pytest.mark.parametrize("nu,nv,p,twins", [(1, 1, 1.0, 0), (40, 65, 0.2, 6), (65, 40, 0.2, 6), (9, 300, 0.6, 2), (90, 90, 0.1, 30)])
+def test_prune_routes_agree(mbe, orc, prune, nu, nv, p, twins):
+    g = _with_twins(gg.random_small(nu, nv, p, 47), twins, 3) if twins else gg.complete(nu, nv)
+    _say("prune routes", prune, nu, nv)
+    want = orc.mbea(g, want_list=True)
+    res, flat = mbe.mbe_enumerate(g, mbe.Options(prune=prune))
+    assert mbe.decode_records(flat) == want["list"]
+    for r in (res, mbe.mbe_count(g, mbe.Options(prune=prune)), mbe.mbe_count(g, mbe.Options(prune=prune, steal_k=3, grid=3)),
+              mbe.mbe_count(g, mbe.Options(prune=prune, diagnostics=True)), mbe.mbe_count_noalloc(g, mbe.Options(prune=prune))):
+        assert [r[k] for k in ("count", "hash", "out_ints", "side")] == [want[k] for k in ("count", "hash", "out_ints", "side")]
+
+
 def test_prune_rejected_where_unsupported(mbe):
     g = gg.crown(5)
     for call in (lambda: mbe.mbe_count_batch([g], mbe.Options(prune=True)),
