@@ -56,7 +56,7 @@ namespace mbe {
 namespace {
 
 constexpr uint64_t kHashK = 0x9E3779B97F4A7C15ull;
-constexpr uint32_t kShared = 0xFFFFFFFFu;
+constexpr uint32_t kShared = 0xFFFFFFFFu;  // frame offset meaning "the workgroup's top-level list"
 // Ticks of the 100 MHz wall clock.  A top-level list is moved out for others only after its
 // workgroup has searched it for 0.3 ms: from then on every claim is an add on one address for all,
 // and the others read the list through their own L2 (a die has its own), so lists of short items
@@ -66,7 +66,7 @@ constexpr uint32_t kShared = 0xFFFFFFFFu;
 // 50 ms with either.
 constexpr uint32_t kShareAfter = 30000;
 constexpr uint32_t kLongItem = 10000;  // an item of 0.1 ms or more is claimed by itself
-constexpr uint32_t kMovedMark = 1u << 30;  // added to the LDS item counter when the list moves  // frame offset meaning "the workgroup's top-level list"
+constexpr uint32_t kMovedMark = 1u << 30;  // added to the LDS item counter when the list moves
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr int kQKeep = 256;      // most incomparable Q' masks a compressed child keeps
 // A compressed child's Q' (entries with two or more bits of R') is reduced to its
