@@ -1377,10 +1377,14 @@ __device__ __forceinline__ void fold_rows(const Ctx &c, const FrameView &v, int 
 }
 
 // What handling a node did: nothing below it, its child frame pushed (state in C), or a child
-// frame that did not fit the stack.  The caller learns of a full stack from here alone: looking
-// at the launch's flag word after every node was a round trip to the L2 on nearly every node
-// (most push nothing).
+// frame that did not fit the stack.  After a node that pushed nothing the caller reads the
+// launch's flag word, so that every wave stops soon after one of them ran out of room (the host
+// then repeats the launch).
 enum class Node : int { kLeaf, kPushed, kFull };
+
+__device__ __forceinline__ bool stack_ran_out(const unsigned int *flags) {
+    return (uni(__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & FLAG_STACK_OVERFLOW) != 0u;
+}
 
 // The candidate at position i of frame F, |R'| = r >= 1, handled by the whole wave (one-word
 // masks: known to be maximal, see light_chunk).  report = false rebuilds the child frame of a
@@ -2946,7 +2950,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                     }
                     ++depth;
                     cur = ch;
-                } else if (node == Node::kFull) {
+                } else if (node == Node::kFull || stack_ran_out(a.flags)) {
                     aborted = true;
                 }
             }
@@ -4058,7 +4062,7 @@ __global__ __launch_bounds__(512) void wide_kernel(SearchArgs a, int64_t lo, int
                     if (TB && ln == 0) acc.dbytes += 2ull * sizeof(FrameState);
                     ++depth;
                     cur = ch;
-                } else if (node == Node::kFull) {
+                } else if (node == Node::kFull || stack_ran_out(a.flags)) {
                     aborted = true;
                 }
             }

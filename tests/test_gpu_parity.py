@@ -234,6 +234,22 @@ def test_node_paths(mbe, orc, nu, nv, p):
     _check(mbe, orc, g, f"nodes {nu}x{nv} k3", side=1, steal_k=3, grid=4)
 
 
+@pytest.mark.parametrize("steal_k", [1, 2, 3])
+def test_stacks_that_run_out(mbe, orc, steal_k):
+    """Nested child lists of up to 675-bit masks outgrow the wave stacks a new server starts with:
+    every wave stops, the launch is repeated with more room, and the answers are the oracle's, those
+    of the graph searched beside it too."""
+    gs = [gg.random_small(9, 900, 0.75, 3), gg.random_small(70, 400, 0.25, 3)]
+    _say("stacks that run out", steal_k)
+    want = [orc.mbea(g) for g in gs]
+    with mbe.Server(slots=1, opt=mbe.Options(steal_k=steal_k, diagnostics=True)) as sv:
+        tks = [sv.submit(g) for g in gs]
+        got = [sv.wait(t)[0] for t in tks]
+    assert got[0]["attempts"] >= 2
+    for r, w in zip(got, want):
+        assert [r[k] for k in DIAG_KEYS] == [w[k] for k in DIAG_KEYS]
+
+
 @pytest.mark.parametrize("n", [40000, 140000])
 def test_long_top_level_lists(mbe, orc, n):
     """x's top-level list has n earlier-ranked entries, so its bitmaps span more than one word
