@@ -697,6 +697,18 @@ __device__ __forceinline__ void write_record(const Ctx &c, const uint64_t *Rr, i
     }
 }
 
+// The lanes of chunk base (one-word masks) whose candidate is the first entry of the list to hold
+// some bit: nothing earlier holds all of its R'.  Lane b turns bit b's first[] entry into a lane
+// of the chunk, and the wave ORs them.
+__device__ __forceinline__ uint64_t first_holders(const FrameState &F, const FrameView &v, int base) {
+    const int ln = lane_id();
+    const uint32_t at = ln < F.rbits ? v.first[ln] - 1u - (uint32_t)base : kNone;
+    const auto either = [](uint32_t a, uint32_t b) { return a | b; };
+    const uint32_t lo = wave_scan32(at < 32u ? 1u << at : 0u, either);
+    const uint32_t hi = wave_scan32(at - 32u < 32u ? 1u << (at - 32u) : 0u, either);
+    return ((uint64_t)(uint32_t)last_lane((int)hi) << 32) | (uint32_t)last_lane((int)lo);
+}
+
 // Maximality of the candidates of chunk base (lane l: position base + l, mask m) whose lanes are
 // in hv, |R'| >= 2, frames of one-word masks: a candidate is not maximal when an earlier entry
 // holds all of R', a bit below its position in the AND of R''s rows.  Returns the lanes that are
@@ -833,7 +845,11 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
     if (DIAG) acc.ph[PH_LIGHT] += clock64() - t0;
     if constexpr (WF == 1) {
         const uint64_t t1 = DIAG ? clock64() : 0ull;
-        if (hv) hv &= ~check_chunk<DIAG, TB>(c, F, v, base, m[0], hv, acc, settle);
+        if (hv) {
+            const uint64_t open = hv & ~first_holders(F, v, base);
+            if (TB && settle && ln == 0) acc.dbytes += 4ull * (uint64_t)F.rbits;
+            if (open) hv &= ~check_chunk<DIAG, TB>(c, F, v, base, m[0], open, acc, settle);
+        }
         if (DIAG) acc.ph[PH_CHECK] += clock64() - t1;
     }
     if (ENUM) {

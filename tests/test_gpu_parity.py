@@ -234,6 +234,16 @@ def test_node_paths(mbe, orc, nu, nv, p):
     _check(mbe, orc, g, f"nodes {nu}x{nv} k3", side=1, steal_k=3, grid=4)
 
 
+# Lists in which most candidates are the first to hold some vertex of R (nothing to test), all but
+# a few are, or none is; lists of one row word, of two and of five, whose chunks of candidates
+# begin anywhere in a word.
+@pytest.mark.parametrize("nu,nv,p", [(40, 64, 0.05), (70, 64, 0.06), (130, 40, 0.06), (300, 200, 0.03), (130, 6, 0.6),
+                                     (64, 1, 1.0), (129, 64, 0.02)])
+def test_first_holders(mbe, orc, nu, nv, p):
+    _check(mbe, orc, gg.random_small(nu, nv, p, 53), f"first holders {nu}x{nv}", side=1)
+    _check(mbe, orc, gg.private_neighbours(nu, 3), f"private {nu}", side=1)
+
+
 @pytest.mark.parametrize("steal_k", [1, 2, 3])
 def test_stacks_that_run_out(mbe, orc, steal_k):
     """Nested child lists of up to 675-bit masks outgrow the wave stacks a new server starts with:
