@@ -432,10 +432,7 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
     dims.waves = waves;
     dims.ucap = (int32_t)std::max<int64_t>(1, std::min<int64_t>(ncand, (int64_t)hstats[9]));
     dims.maxdepth = 64 * Wmax + 2;
-    // (frames keep no words for Q entries, and the stack gives up what the frame headers and the
-    // list's record for other workgroups take: an arena slot is never larger than 4 ucap + 16384
-    // words per stack made it, so a caller's memory that held one still does)
-    dims.scap = 4 * (int64_t)dims.ucap + 16384 - 2 * (int64_t)dims.maxdepth - 256;
+    dims.scap = 4 * (int64_t)dims.ucap + 16384;
 
     if (ws_out) {
         int64_t cls_a[5], cls_b[5];

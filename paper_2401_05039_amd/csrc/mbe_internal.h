@@ -82,7 +82,8 @@ struct ArenaLayout {
     size_t off_hb;      // u64[ucap/64+1]       top-level candidates with |R'| >= 2, per chunk
     size_t off_hpre;    // u32[ucap/64+2]       popcount prefix of those words
     size_t off_hpos;    // u32[ucap]            their positions, in list order
-    size_t off_top;     // the list's frame state and sizes, for workgroups that share it
+    size_t off_top;     // the list's frame state and sizes, for workgroups that share it (in the
+                        // staged counts' place)
     size_t s1_words;
     size_t off_waves;   // start of the per-wave regions
     size_t wave_bytes;  // stride between waves

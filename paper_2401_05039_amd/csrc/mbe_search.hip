@@ -249,16 +249,17 @@ struct FrameState {
     int32_t nq;
     int32_t level;   // search depth of the candidates taken from this list (top level = 1)
     int32_t nL;      // |L| of the nodes below
-    int32_t wf;      // mask words per entry
-    int32_t narrow;  // 1: bits are compressed positions of R, mapped by orig[] to N(x) positions
+    int32_t narrow;  // 1: one-word masks of compressed positions of R, mapped by orig[] to N(x) positions
     int32_t chunk;   // base position of the current 64-candidate chunk
     int32_t rbits;   // rows held by the frame: mask bits [0, rbits) can be set
+    int32_t nm;      // the method's |P| + |Q| of the list, tallies of diagnostics mode only
     uint64_t heavy;  // lanes of the current chunk still to be handled one by one
     uint64_t sL;     // sum of the L-side hash terms of L
     uint64_t fw;     // sum over the list of (2 + deg v), byte tally only
-    int32_t nm;      // the method's |P| + |Q| of the list, tallies of diagnostics mode only
-    int32_t pad;
 };
+// (an arena slot holds one header per depth and wave: its size is part of what a caller's memory has
+// room for)
+static_assert(sizeof(FrameState) == 64, "frame headers");
 
 __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
     FrameState u;
@@ -268,7 +269,6 @@ __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
     u.nq = uni(f.nq);
     u.level = uni(f.level);
     u.nL = uni(f.nL);
-    u.wf = uni(f.wf);
     u.narrow = uni(f.narrow);
     u.chunk = uni(f.chunk);
     u.rbits = uni(f.rbits);
@@ -276,7 +276,6 @@ __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
     u.sL = uni(f.sL);
     u.fw = uni(f.fw);
     u.nm = uni(f.nm);
-    u.pad = 0;
     return u;
 }
 
@@ -1203,7 +1202,6 @@ __device__ __forceinline__ bool build_narrow(const Ctx &c, const FrameState &F, 
     C.top = top2;
     C.n = n2;
     C.nq = nq2;
-    C.wf = 1;
     C.narrow = 1;
     C.chunk = nq2 - 64;
     C.rbits = r;
@@ -1363,7 +1361,6 @@ __device__ __forceinline__ bool build_wide(const Ctx &c, const FrameState &F, co
     C.top = top2;
     C.n = n2;
     C.nq = nq2;
-    C.wf = W;
     C.narrow = 0;
     C.chunk = nq2 - 64;
     C.rbits = bits;
@@ -1673,7 +1670,6 @@ __device__ __forceinline__ Node heavy_node(const Ctx &c, const FrameState &F, co
     C.sL = sL;
     C.fw = DIAG ? wave_sum_u64(fwc) : 0ull;
     C.nm = qn + pn;
-    C.pad = 0;
     if (DIAG) acc.ph[PH_CHILD] += clock64() - tp;
     return Node::kPushed;
 }
@@ -2669,7 +2665,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         top.nq = nqk;
         top.level = 2;
         top.nL = 1 + sh->nexp;
-        top.wf = W;
         top.narrow = 0;
         top.chunk = 0;
         top.rbits = d;
@@ -2677,7 +2672,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         top.sL = hl(c, x) + sh->exps;
         top.fw = uni((uint64_t)sh->fw1);
         top.nm = nq0 + P1;
-        top.pad = 0;
         if (ENUM) {  // for the records of the top-level light pass
             c.trows = v1.rows;
             c.tids = v1.ids;
@@ -2793,7 +2787,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
             FrameState cur = uni_frame(sh->topf);
             int depth = 0;
             while (!aborted) {
-                const FrameView v = frame_view(frame_base(c, cur.off), cur.n, cur.nq, cur.wf, DIAG || cur.off == kShared);
+                const FrameView v = frame_view(frame_base(c, cur.off), cur.n, cur.nq, cur.narrow ? 1 : W, DIAG || cur.off == kShared);
                 int i;
                 if (depth == 0) {
                     if (src_top) {
@@ -2941,7 +2935,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                             continue;
                         }
                         cur.chunk = base;
-                        cur.heavy = (cur.wf == 1) ? light_chunk<1, DIAG, ENUM, TB>(c, cur, v, base, acc)
+                        cur.heavy = (W == 1 || cur.narrow) ? light_chunk<1, DIAG, ENUM, TB>(c, cur, v, base, acc)
                                                   : light_chunk<W, DIAG, ENUM, TB>(c, cur, v, base, acc);
                         continue;
                     }
@@ -2951,7 +2945,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                 }
                 FrameState ch;
                 const bool report = src_top || depth > 0;
-                const Node node = (cur.wf == 1) ? heavy_node<1, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report)
+                const Node node = (W == 1 || cur.narrow) ? heavy_node<1, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report)
                                                 : heavy_node<W, W, DIAG, ENUM, TB>(c, cur, v, i, ch, acc, report);
                 if (node == Node::kPushed) {
                     if (depth >= a.dims.maxdepth) {
@@ -3588,7 +3582,6 @@ __device__ __forceinline__ Node heavy_wide(const WCtx &w, const FrameState &F, c
     C.nq = qn;
     C.level = F.level + 1;
     C.nL = nL;
-    C.wf = wf2;
     C.narrow = 1;
     C.chunk = qn - 64;
     C.rbits = r;
@@ -4027,7 +4020,6 @@ __global__ __launch_bounds__(512) void wide_kernel(SearchArgs a, int64_t lo, int
         top.nq = n1 - P1c;
         top.level = 2;
         top.nL = 1 + uni(sh->nexp);
-        top.wf = wd;
         top.narrow = 1;
         top.chunk = 0;
         top.rbits = d;
@@ -4244,14 +4236,15 @@ ArenaLayout search_layout(const SearchDims &d) {
     L.off_hv = take(bits * 8);
     L.off_deg = take(bits * 4);
     L.off_t1v = take(ucap * 4);
-    L.off_t1c = take(ucap * 4);
+    // (the staged counts are used while the top-level list is built, its record only after that)
+    static_assert(sizeof(TopRec) <= 256, "the record fits the smallest region");
+    L.off_top = L.off_t1c = take(ucap * 4);
     // ids | hs | masks | first, cnt | H | orig | rows (see frame_view)
     L.s1_words = align_up(ucap, 2) + 2 * ucap + 2 * ucap * W + 2 * bits + 2 * bits + 64 + 128 + 2 * bits * ((ucap + 63) / 64) + 2;
     L.off_S1 = take(L.s1_words * 4);
     L.off_hb = take((ucap / 64 + 1) * 8);
     L.off_hpre = take((ucap / 64 + 2) * 4);
     L.off_hpos = take(ucap * 4);
-    L.off_top = take(sizeof(TopRec));
     L.off_waves = o;
     size_t w = 0;
     auto wtake = [&](size_t bytes) {
