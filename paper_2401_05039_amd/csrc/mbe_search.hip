@@ -72,7 +72,10 @@ constexpr int kQKeep = 256;      // most incomparable Q' masks a compressed chil
 // A compressed child's Q' (entries with two or more bits of R') is reduced to its
 // inclusion-maximal masks when it has more than this many entries.  The reduction compares every
 // entry with the masks kept so far; below the line the AND of a few more row words per check
-// costs less.
+// costs less.  (Also where the row words of the whole Q' would make the frame larger than one with
+// the reduced entries' ids, hash terms and masks, the candidates' ids and tables for 64 bits: that
+// was the frame's size before Q' became rows alone, and a caller's memory that held it holds this.
+// Reducing wherever it saves a row word took the power-law graph from 19.8 to 20.9 ms.)
 constexpr int kQReduce = 256;
 // A maximal node's P' positions (stu) stay in the wave's LDS for lists of at most this many
 // candidates, in global scratch for longer ones.
@@ -279,9 +282,10 @@ __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
     return u;
 }
 
-// Word layout of a frame's data starting at a 2-aligned offset o (np = n - nq candidates):
-//   ids[n] | hs[np] (u64) | masks[np][wf] (u64) | first[64wf] | cnt[64wf] | H[64wf] (u64) |
-//   orig[64] | hR[64] (u64) | rows[rbits][nw] (u64), nw = ceil(n / 64)
+// Word layout of a frame's data starting at a 2-aligned offset o (np = n - nq candidates; tb table
+// bits, see table_bits):
+//   ids[n] | hs[np] (u64) | masks[np][wf] (u64) | H[tb] (u64) | hR[tb] (u64) | first[tb] | cnt[tb] |
+//   orig[tb] | rows[rbits][nw] (u64), nw = ceil(n / 64)
 // ids are universe indices; a child frame has them in diagnostics mode only.  hs is the L-side
 // hash term and masks the mask of each candidate.  Row b is the position bitmap of mask bit b:
 // bit k % 64 of its word k / 64 is set when entry k holds bit b; only bits [0, rbits) can be
@@ -291,7 +295,7 @@ __device__ __forceinline__ FrameState uni_frame(const FrameState &f) {
 // first / cnt / H: per bit, 1 + the first candidate position holding it, or 0 when some Q entry
 // holds it (a Q entry with a single bit of R witnesses nothing else: outside diagnostics mode it
 // is left out of the rows); how many candidates hold it, and the sum of their hash terms
-// (valid for bits below rbits).
+// (valid for bits below rbits).  hR and orig: narrow frames only.
 struct FrameView {
     const uint32_t *ids;
     const uint64_t *hs;
@@ -305,21 +309,26 @@ struct FrameView {
     int nw;
 };
 
-__device__ __forceinline__ uint32_t frame_words_fixed(int n, int nq, int wf, int rbits, bool ids) {
-    const uint32_t bits = 64u * (uint32_t)wf, nw = ((uint32_t)n + 63u) >> 6, np = (uint32_t)(n - nq);
+// Entries of a frame's per-bit tables: a narrow frame's own bits, else whole mask words.  (A frame
+// with tables for 64 bits whatever |R| had 448 words of them; most frames of sparse graphs hold
+// fewer than ten bits.)
+__device__ __forceinline__ uint32_t table_bits(bool narrow, int wf, int rbits) {
+    return narrow ? (uint32_t)rbits : 64u * (uint32_t)wf;
+}
+
+__device__ __forceinline__ uint32_t frame_words_fixed(int n, int nq, int wf, int rbits, bool narrow, bool ids) {
+    const uint32_t tb = table_bits(narrow, wf, rbits), nw = ((uint32_t)n + 63u) >> 6, np = (uint32_t)(n - nq);
     uint32_t o = ids ? align2((uint32_t)n) : 0u;
-    o += 2u * np;                          // hs
-    o += 2u * np * (uint32_t)wf;           // masks
-    o += 2u * bits;                        // first, cnt
-    o += 2u * bits;                        // H
-    o += 64u;                              // orig
-    o += 128u;                             // hR
-    o += 2u * (uint32_t)rbits * nw;        // rows
+    o += 2u * np;                           // hs
+    o += 2u * np * (uint32_t)wf;            // masks
+    o += 4u * tb;                           // H, first, cnt
+    o += narrow ? align2(3u * tb) : 0u;     // hR, orig
+    o += 2u * (uint32_t)rbits * nw;         // rows
     return o;
 }
 
-__device__ __forceinline__ FrameView frame_view(uint32_t *base, int n, int nq, int wf, bool ids) {
-    const uint32_t bits = 64u * (uint32_t)wf, np = (uint32_t)(n - nq);
+__device__ __forceinline__ FrameView frame_view(uint32_t *base, int n, int nq, int wf, int rbits, bool narrow, bool ids) {
+    const uint32_t tb = table_bits(narrow, wf, rbits), np = (uint32_t)(n - nq);
     FrameView v;
     v.nw = (n + 63) >> 6;
     v.ids = base;
@@ -328,16 +337,14 @@ __device__ __forceinline__ FrameView frame_view(uint32_t *base, int n, int nq, i
     o += 2u * np;
     v.masks = reinterpret_cast<const uint64_t *>(base + o);
     o += 2u * np * (uint32_t)wf;
-    v.first = base + o;
-    o += bits;
-    v.cnt = base + o;
-    o += bits;
     v.H = reinterpret_cast<uint64_t *>(base + o);
-    o += 2u * bits;
-    v.orig = base + o;
-    o += 64u;
+    o += 2u * tb;
     v.hR = reinterpret_cast<uint64_t *>(base + o);
-    o += 128u;
+    if (narrow) o += 2u * tb;
+    v.first = base + o;
+    v.cnt = v.first + tb;
+    v.orig = v.cnt + tb;
+    o += narrow ? align2(3u * tb) : 2u * tb;
     v.rows = reinterpret_cast<uint64_t *>(base + o);
     return v;
 }
@@ -1030,7 +1037,7 @@ __device__ __forceinline__ bool build_narrow(const Ctx &c, const FrameState &F, 
         __builtin_amdgcn_wave_barrier();
         nq2 = __popcll(mx);
         listed = true;
-    } else if (!DIAG && g.qn > kQReduce) {
+    } else if (!DIAG && (g.qn > kQReduce || 2 * r * (((g.qn + pn + 63) >> 6) - ((pn + 64) >> 6)) > pn + 4 + 7 * (64 - r))) {
         const int nk = reduce_q(c, v, g.i, r, bt, g.nzq);
         if (nk >= 0) {
             nq2 = nk;
@@ -1039,13 +1046,13 @@ __device__ __forceinline__ bool build_narrow(const Ctx &c, const FrameState &F, 
     }
     const int n2 = nq2 + pn, nw2 = (n2 + 63) >> 6;
     const uint32_t off2 = F.top;
-    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, nq2, 1, r, DIAG));
+    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, nq2, 1, r, true, DIAG));
     if ((int64_t)top2 > c.scap) {
         if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_STACK_OVERFLOW);
         return false;
     }
     uint32_t *cb = c.stk + off2;
-    const FrameView v2 = frame_view(cb, n2, nq2, 1, DIAG);
+    const FrameView v2 = frame_view(cb, n2, nq2, 1, r, true, DIAG);
     uint64_t *hs2 = const_cast<uint64_t *>(v2.hs);
     uint64_t *masks2 = const_cast<uint64_t *>(v2.masks);
     int c0 = 0;  // row words written so far; entries from 64 c0 on wait in c.qk
@@ -1209,26 +1216,79 @@ __device__ __forceinline__ bool build_narrow(const Ctx &c, const FrameState &F, 
     return true;
 }
 
-// The child list of a maximal node with |R'| > 64: masks keep the frame's W words, Q' is the
-// frame's rows of R' up to the node, position for position, and P' follows from there.
+// The child list of a maximal node with |R'| > 64: masks keep the frame's W words, P' follows Q' in
+// the rows.  Q' is the frame's rows of R' up to the node, position for position; or, where the words
+// of the positions that are not in Q' (those holding no bit of R', with diagnostics off also those
+// holding one, which first[] stands for) would take more room than the Q' entries' own ids, hash
+// terms and masks would, the positions of Q' alone.
 template <int W, bool DIAG, bool TB>
 __device__ __forceinline__ bool build_wide(const Ctx &c, const FrameState &F, const FrameView &v, const Grown<W> &g,
                                            FrameState &C, WaveAcc &acc, bool tally, uint64_t &fwc) {
     constexpr int bits = 64 * W;
     const int ln = lane_id(), r = g.r, pn = g.pn, wi = g.i >> 6;
     const uint64_t below = lanes_below();
-    const int nq2 = g.i, n2 = nq2 + pn, nw2 = (n2 + 63) >> 6;
+    const bool compact =
+        (int64_t)2 * bits * (((g.i + pn + 63) >> 6) - ((g.qn + pn + 63) >> 6)) + (DIAG ? g.i - g.qn : 0) >
+        (DIAG ? (int64_t)g.qn * (2 * W + 2) : (int64_t)g.qn * (2 * W + 3) + pn);
+    const int nq2 = compact ? g.qn : g.i, n2 = nq2 + pn, nw2 = (n2 + 63) >> 6;
     const uint32_t off2 = F.top;
-    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, nq2, W, bits, DIAG));
+    const uint32_t top2 = align2(off2 + frame_words_fixed(n2, nq2, W, bits, false, DIAG));
     if ((int64_t)top2 > c.scap) {
         if (ln == 0) atomicOr(c.flags, (unsigned int)FLAG_STACK_OVERFLOW);
         return false;
     }
     uint32_t *cb = c.stk + off2;
-    const FrameView v2 = frame_view(cb, n2, nq2, W, DIAG);
+    const FrameView v2 = frame_view(cb, n2, nq2, W, bits, false, DIAG);
     uint64_t *hs2 = const_cast<uint64_t *>(v2.hs);
     uint64_t *masks2 = const_cast<uint64_t *>(v2.masks);
-    for (int base = 0; base < wi; base += 64) {
+    int q2 = 0;  // Q' positions written
+    for (int base = 0; compact && base <= wi; base += 64) {
+        // the words' positions of Q', a word per lane; then, a bit of R' per lane, their bits of its row
+        const int wd = base + ln;
+        uint64_t u = 0ull, tw = 0ull;
+        for (int t = 0; t < r; t += 4) {
+            uint32_t b[4];
+            uint64_t x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[q] = uni(c.hist[t + q < r ? t + q : t]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = wd <= wi ? v.rows[(size_t)b[q] * v.nw + wd] : 0ull;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (t + q < r) tw |= u & x[q];
+                u |= x[q];
+            }
+        }
+        const uint64_t keep = (DIAG ? u : tw) & (wd < wi ? ~0ull : wd == wi ? (1ull << (g.i & 63)) - 1ull : 0ull);
+        const uint64_t nz = __ballot(keep != 0ull);
+        const int incl = wave_incl_scan(__popcll(keep));
+        if (DIAG) {
+            int at = q2 + incl - __popcll(keep);
+            for (uint64_t f = keep; f; f &= f - 1ull) cb[at++] = v.ids[64 * wd + __ffsll((unsigned long long)f) - 1];
+        }
+        for (int t0 = 0; t0 < r; t0 += 64) {
+            const bool on = t0 + ln < r;
+            const uint32_t b = on ? c.hist[t0 + ln] : 0u;
+            const uint64_t *src = v.rows + (size_t)b * v.nw + base;
+            uint64_t *dst = v2.rows + (size_t)b * nw2;
+            int at = q2;
+            uint64_t out = on && (at & 63) ? dst[at >> 6] : 0ull;
+            for (uint64_t z = nz; z; z &= z - 1ull) {  // uniform
+                const int l = __ffsll((unsigned long long)z) - 1, sh = at & 63;
+                const uint64_t k = readlane64(keep, l);
+                const uint64_t x = compress_word(on ? src[l] : 0ull, k, 0);
+                out |= x << sh;
+                at += __popcll(k);
+                if (sh + __popcll(k) >= 64) {
+                    if (on) dst[(at >> 6) - 1] = out;
+                    out = sh ? x >> (64 - sh) : 0ull;
+                }
+            }
+            if (on && (at & 63)) dst[at >> 6] = out;
+        }
+        q2 += last_lane(incl);
+    }
+    for (int base = 0; !compact && base < wi; base += 64) {
         const int wd = base + ln;
         for (int t = 0; t < r; t += 4) {
             uint32_t b[4];
@@ -1251,7 +1311,7 @@ __device__ __forceinline__ bool build_wide(const Ctx &c, const FrameState &F, co
         v2.cnt[b] = 0u;
         v2.H[b] = 0ull;
     }
-    if (DIAG)
+    if (DIAG && !compact)
         for (int p = ln; p < nq2; p += 64) cb[p] = v.ids[p];
     wait_mem();
     __builtin_amdgcn_wave_barrier();
@@ -1328,21 +1388,23 @@ __device__ __forceinline__ bool build_wide(const Ctx &c, const FrameState &F, co
         __builtin_amdgcn_wave_barrier();
     }
     see_atomics();
-    // the word holding the node's position on: Q' below it, then P'
-    const int sh = g.i & 63;
+    // the word in which Q' ends: its last positions, then P'
+    const int sh = nq2 & 63, w0 = nq2 >> 6;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         if (!g.m[w]) continue;  // uniform: rows of the other words are never read
         const size_t b = (size_t)(64 * w + ln);
-        uint64_t carry = (g.m[w] >> ln) & 1ull ? v.rows[b * v.nw + wi] & ((1ull << sh) - 1ull) : 0ull;
+        uint64_t carry = 0ull;
+        if (sh && ((g.m[w] >> ln) & 1ull))
+            carry = compact ? v2.rows[b * nw2 + w0] : v.rows[b * v.nw + wi] & ((1ull << sh) - 1ull);
         int q = 0;
         for (; 64 * q < pn; ++q) {
             const int e = 64 * q + ln;
             const uint64_t t = wave_transpose64(e < pn ? masks2[(size_t)e * W + w] : 0ull);
-            v2.rows[b * nw2 + wi + q] = carry | (t << sh);
+            v2.rows[b * nw2 + w0 + q] = carry | (t << sh);
             carry = sh ? t >> (64 - sh) : 0ull;
         }
-        if (wi + q < nw2) v2.rows[b * nw2 + wi + q] = carry;
+        if (w0 + q < nw2) v2.rows[b * nw2 + w0 + q] = carry;
     }
     wait_mem();
     if (TB && tally) {
@@ -1353,9 +1415,11 @@ __device__ __forceinline__ bool build_wide(const Ctx &c, const FrameState &F, co
         for (int w = 0; w < W; ++w) nzw += g.m[w] ? 1 : 0;
         acc.dbytes += 16ull * tbits;
         if (ln == 0)
-            acc.dbytes += 16ull * (uint64_t)r * (uint64_t)wi + 8ull * (uint64_t)r + 16ull * bits +
+            acc.dbytes += (compact ? 16ull * (uint64_t)r * (uint64_t)(wi + 1) + 8ull * (uint64_t)r * (uint64_t)w0
+                                   : 16ull * (uint64_t)r * (uint64_t)wi) +
+                          8ull * (uint64_t)r + 16ull * bits +
                           (uint64_t)pn * (16ull + 24ull * (uint64_t)nzw + 8ull * W) +
-                          8ull * 64ull * (uint64_t)nzw * (uint64_t)(nw2 - wi);
+                          8ull * 64ull * (uint64_t)nzw * (uint64_t)(nw2 - w0);
     }
     C.off = off2;
     C.top = top2;
@@ -2573,7 +2637,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
 
         // -- the top-level child list as a frame: ids Q1 (earlier ranks) ++ P1 sorted by
         //    count, masks over the positions of N(x), per-bit tables
-        FrameView v1 = frame_view(s1, n1, nqk, W, true);
+        FrameView v1 = frame_view(s1, n1, nqk, W, d, false, true);
         if (wid == 0) {
             int pn = 0;
             for (int base = nq0; base < s0; base += 64) {
@@ -2739,7 +2803,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
         const int H = uni(sh->H);
         c.s0 = uni(sh->us0);
         if (ENUM) {
-            const FrameView tv = frame_view(c.s1, top.n, top.nq, W, true);
+            const FrameView tv = frame_view(c.s1, top.n, top.nq, W, top.rbits, false, true);
             c.trows = tv.rows;
             c.tids = tv.ids;
             c.tnw = tv.nw;
@@ -2787,7 +2851,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
             FrameState cur = uni_frame(sh->topf);
             int depth = 0;
             while (!aborted) {
-                const FrameView v = frame_view(frame_base(c, cur.off), cur.n, cur.nq, cur.narrow ? 1 : W, DIAG || cur.off == kShared);
+                const FrameView v = frame_view(frame_base(c, cur.off), cur.n, cur.nq, cur.narrow ? 1 : W, cur.rbits, cur.narrow != 0,
+                                               DIAG || cur.off == kShared);
                 int i;
                 if (depth == 0) {
                     if (src_top) {

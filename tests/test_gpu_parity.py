@@ -260,6 +260,24 @@ def test_stacks_that_run_out(mbe, orc, steal_k):
         assert [r[k] for k in DIAG_KEYS] == [w[k] for k in DIAG_KEYS]
 
 
+# Hubs among many candidates of few neighbours: a child list of more than 64 bits has a thousand
+# entries before it, of which few hold two or more of its vertices.  Kept position for position they
+# overran the stacks a call starts with (two launches), where their own rows fit.
+@pytest.mark.parametrize("n_low,hubs,lo,hi,n_v", [(1000, 5, 500, 700, 4000), (3000, 6, 900, 1000, 9000), (600, 8, 130, 256, 1500)])
+def test_sparse_lists_of_hubs(mbe, orc, n_low, hubs, lo, hi, n_v):
+    rng = np.random.default_rng(7)
+    rows = [rng.choice(n_v, 4, replace=False) for _ in range(n_low)]
+    rows += [rng.choice(n_v, int(rng.integers(lo, hi + 1)), replace=False) for _ in range(hubs)]
+    g = gg.from_edges(len(rows), n_v, np.repeat(np.arange(len(rows)), [len(r) for r in rows]), np.concatenate(rows))
+    _check(mbe, orc, g, f"hub lists {n_low}")
+    _check(mbe, orc, g, f"hub lists {n_low} k3", steal_k=3, grid=4)
+    want = orc.mbea(g, want_list=True)
+    assert mbe.decode_records(mbe.mbe_enumerate(g)[1]) == want["list"]
+    with mbe.Server(slots=1) as sv:  # (a new server's slots have the room that a first call starts with)
+        r, _ = sv.wait(sv.submit(g))
+    assert (r["count"], r["hash"], r["attempts"]) == (want["count"], want["hash"], 1)
+
+
 @pytest.mark.parametrize("n", [40000, 140000])
 def test_long_top_level_lists(mbe, orc, n):
     """x's top-level list has n earlier-ranked entries, so its bitmaps span more than one word
