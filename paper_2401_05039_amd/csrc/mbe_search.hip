@@ -500,6 +500,15 @@ struct RecPlace {
     }
 };
 
+// Whether records of len ints in all are asked for by themselves by a wave whose next reservation
+// holds kRecInts ints for each of bi records: those of more than an eighth of it.  (Written without
+// a product of len, which wraps from 2^29 ints on.)
+__host__ __device__ constexpr bool by_itself(unsigned int len, unsigned int bi) { return len > kRecInts / 8u * bi; }
+static_assert(kRecInts % 8u == 0u && !by_itself(8u, kRecBatch0) && by_itself(9u, kRecBatch0) &&
+                  !by_itself(128u, kRecBatchMax) && by_itself(129u, kRecBatchMax) &&
+                  by_itself((1u << 29) + 3u, kRecBatchMax) && by_itself(0xFFFFFFFFu, kRecBatchMax),
+              "reservations of any length");
+
 // Reserves n records of len ints in all (one wave).  The arena's counters are one address for the
 // whole device, which takes an atomic every 8 to 16 ns: with two per record, listing a power-law
 // graph of 20,000 x 10,000 vertices (516,620 records) took three times its search, 6.5 ms against
@@ -534,7 +543,7 @@ __device__ __forceinline__ RecPlace reserve_records(const Ctx &c, unsigned int l
     const uint64_t st = uni((uint64_t)c.res[2]), gr = uni((uint64_t)c.res[3]);
     unsigned int left = (unsigned int)st, bi = (unsigned int)gr, bn = (unsigned int)(gr >> 32);
     int ileft = (int)(st >> 32);
-    const bool more_i = len > left, direct = more_i && 8u * len > kRecInts * bi, more_n = n > ileft;
+    const bool more_i = len > left, direct = more_i && by_itself(len, bi), more_n = n > ileft;
     if (more_i || more_n) {
         const unsigned int ai = !more_i ? 0u : direct ? len : kRecInts * bi;
         const unsigned int an = more_n ? (unsigned int)(n - ileft) + bn - 1u : 0u;
@@ -640,34 +649,41 @@ __device__ __forceinline__ void write_record_rows(const Ctx &c, int nL, int r) {
 }
 
 // The records of a chunk's maximal nodes of |R'| = 1 (lanes in own; lane l's R' is position rp of
-// N(x_root), its L' has nL vertices), reserved together.  c.tfull == 0 as above.
+// N(x_root), its L' has nL vertices), reserved together, or one by one where any has 2^24 vertices
+// (the lengths of 64 such records need not add up in 32 bits).  c.tfull == 0 as above.
 __device__ __forceinline__ void write_leaf_records(const Ctx &c, uint64_t own, uint32_t rp, int nL) {
     const int ln = lane_id();
-    const bool mine = (own >> ln) & 1ull;
-    const int len = mine ? 3 + nL : 0;
-    const int incl = wave_incl_scan(len);
-    const RecPlace p = reserve_records(c, (unsigned int)last_lane(incl), __popcll(own));
-    const unsigned long long off = p.off + (unsigned long long)(unsigned int)(incl - len);
-    const unsigned long long idx = p.index(__popcll(own & lanes_below()));
-    const bool fits = mine && off + (unsigned long long)len <= c.rec_cap && idx < c.rec_offs_cap;
-    if (mine && !fits) atomicOr(c.flags, (unsigned int)FLAG_RECORD_OVERFLOW);
-    if (fits) {
-        int32_t *o = c.rec + off;
-        o[0] = c.c_is_v ? 1 : nL;
-        o[1] = c.c_is_v ? nL : 1;
-        c.rec_offs[idx] = off;
-        o[2 + (c.c_is_v ? 1 : 0)] = c.x_root - c.cbase;
-        o[2 + (c.c_is_v ? 0 : nL)] = c.row[rp] - c.obase;
-    }
-    for (uint64_t q = __ballot(fits); q; q &= q - 1ull) {
-        const int l = __ffsll((unsigned long long)q) - 1;
-        int32_t *pl = c.rec + readlane64(off, l) + 2 + (c.c_is_v ? 1 : 0);
-        const uint64_t *row = c.trows + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)rp, l) * c.tnw;
-        const int n = __builtin_amdgcn_readlane(nL, l);
-        int k = 1;
-        for (int base = 0; base < c.tnw; base += 64) {
-            const int wd = base + ln;
-            k = write_members(c, wd < c.tnw ? row[wd] : 0ull, wd, pl, k, n);
+    const bool apart = __ballot(((own >> ln) & 1ull) && nL >= 1 << 24) != 0ull;
+#pragma unroll 1
+    for (uint64_t rest = own; rest;) {
+        const uint64_t now = apart ? rest & (0ull - rest) : rest;
+        rest &= ~now;
+        const bool mine = (now >> ln) & 1ull;
+        const int len = mine ? 3 + nL : 0;
+        const int incl = wave_incl_scan(len);
+        const RecPlace p = reserve_records(c, (unsigned int)last_lane(incl), __popcll(now));
+        const unsigned long long off = p.off + (unsigned long long)(unsigned int)(incl - len);
+        const unsigned long long idx = p.index(__popcll(now & lanes_below()));
+        const bool fits = mine && off + (unsigned long long)len <= c.rec_cap && idx < c.rec_offs_cap;
+        if (mine && !fits) atomicOr(c.flags, (unsigned int)FLAG_RECORD_OVERFLOW);
+        if (fits) {
+            int32_t *o = c.rec + off;
+            o[0] = c.c_is_v ? 1 : nL;
+            o[1] = c.c_is_v ? nL : 1;
+            c.rec_offs[idx] = off;
+            o[2 + (c.c_is_v ? 1 : 0)] = c.x_root - c.cbase;
+            o[2 + (c.c_is_v ? 0 : nL)] = c.row[rp] - c.obase;
+        }
+        for (uint64_t q = __ballot(fits); q; q &= q - 1ull) {
+            const int l = __ffsll((unsigned long long)q) - 1;
+            int32_t *pl = c.rec + readlane64(off, l) + 2 + (c.c_is_v ? 1 : 0);
+            const uint64_t *row = c.trows + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)rp, l) * c.tnw;
+            const int n = __builtin_amdgcn_readlane(nL, l);
+            int k = 1;
+            for (int base = 0; base < c.tnw; base += 64) {
+                const int wd = base + ln;
+                k = write_members(c, wd < c.tnw ? row[wd] : 0ull, wd, pl, k, n);
+            }
         }
     }
 }
