@@ -691,7 +691,8 @@ __device__ __forceinline__ void write_leaf_records(const Ctx &c, uint64_t own, u
 // Write the record of the maximal biclique (L', R') of a node.  R' is given as positions of
 // N(x_root) (Rr, Wroot words).  L' = {x_root} u {universe v : M[v] contains R'}: every vertex
 // adjacent to all of R'.  Sides are sorted later by the canonicaliser.
-__device__ __forceinline__ void write_record(const Ctx &c, const uint64_t *Rr, int nL, int r) {
+template <typename R>  // global or LDS words
+__device__ __forceinline__ void write_record(const Ctx &c, const R *Rr, int nL, int r) {
     const int ln = lane_id();
     const uint64_t below = lanes_below();
     int32_t *pl, *pr;
@@ -1690,19 +1691,20 @@ __device__ __forceinline__ Node heavy_node(const Ctx &c, const FrameState &F, co
                 write_record_rows(c, nL, r);
             }
         } else {
-            uint64_t Rr[16];
-            for (int w = 0; w < 16; ++w) Rr[w] = 0ull;
+            // R' as positions of N(x_root), in the Q' masks' place (an array of the lane's own went to
+            // registers and took a hundred others to scratch memory)
+            __builtin_amdgcn_wave_barrier();
+            if (ln < W) c.qk[ln] = 0ull;
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int w = 0; w < WF; ++w) {
-                uint64_t mm = g.m[w];
-                while (mm) {
-                    const int b = 64 * w + __ffsll((unsigned long long)mm) - 1;
-                    mm &= mm - 1ull;
-                    const uint32_t rp = root_pos(F, v, (uint32_t)b);
-                    Rr[rp >> 6] |= 1ull << (rp & 63);
+            for (int w = 0; w < WF; ++w)
+                if ((g.m[w] >> ln) & 1ull) {
+                    const uint32_t rp = root_pos(F, v, (uint32_t)(64 * w + ln));
+                    bm_or(&c.qk[rp >> 6], 1ull << (rp & 63));
                 }
-            }
-            write_record(c, Rr, nL, r);
+            __builtin_amdgcn_wave_barrier();
+            write_record(c, c.qk, nL, r);
+            __builtin_amdgcn_wave_barrier();
         }
     }
     if (DIAG && report) {
@@ -2600,12 +2602,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
             }
         }
         if (ENUM && !root_nonmax && wid == 0) {
-            uint64_t R1[16];
-            for (int w = 0; w < 16; ++w) {
-                const int bits = d - 64 * w;
-                R1[w] = bits >= 64 ? ~0ull : (bits <= 0 ? 0ull : ((1ull << bits) - 1ull));
-            }
-            write_record(c, R1, 1 + sh->nexp, d);
+            if (ln < W) c.qk[ln] = d - 64 * ln >= 64 ? ~0ull : d > 64 * ln ? (1ull << (d - 64 * ln)) - 1ull : 0ull;
+            __builtin_amdgcn_wave_barrier();
+            write_record(c, c.qk, 1 + sh->nexp, d);
         }
         if (root_nonmax || P1 == 0) {
             __syncthreads();
