@@ -42,11 +42,17 @@ struct DevBuf {
         size_t want = n < 256 ? 256 : n;
         hipError_t e = hipMalloc(&p, want);
         if (e != hipSuccess) {
+            (void)hipGetLastError();  // (reported here, not by a later launch)
             p = nullptr;
             return e;
         }
         bytes = want;
         return hipSuccess;
+    }
+    void release() {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+        bytes = 0;
     }
     template <typename T>
     T *as(size_t byte_off = 0) const {
@@ -230,10 +236,11 @@ size_t search_footprint(DeviceState *st, SearchDims dims, const int64_t *cls_lo,
 
 // mbe_count / mbe_enumerate; with ws_out, only the preparation runs and *ws_out receives the
 // device bytes the search of this call would hold; with fixed (mbe_count_noalloc), every
-// device buffer of the call is carved from the device's scratch and nothing is allocated
+// device buffer of the call is carved from the device's scratch and nothing is allocated; with spare
+// (mbe_enumerate), the record buffers start anew and are the smallest that will do
 int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t *ubuf, uint64_t ucap_ints,
         int ubuf_on_device, bool enumerate, size_t *ws_out = nullptr, bool fixed = false,
-        std::vector<unsigned long long> *loads = nullptr) {
+        std::vector<unsigned long long> *loads = nullptr, bool spare = false) {
     if (!g || !out) return MBE_ERR_INVALID_ARG;
     std::memset(out, 0, sizeof(*out));
     if (g->n_u < 0 || g->n_v < 0 || g->n_edges < 0) return MBE_ERR_INVALID_ARG;
@@ -451,9 +458,10 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
     // record arena for mbe_enumerate
     unsigned long long rec_cap = 0, offs_cap = 0;
     bool rec_batch = false;
+    if (spare)
+        for (DevBuf *b : {&st->rec, &st->rec_offs, &st->rec_tmp, &st->rec_lens, &st->canon_tmp, &st->out_tmp}) b->release();
     if (enumerate) {
-        // Waves keep reserves of the arena (see reserve_records) where its ints fit 32 bits and
-        // memory has room.  A wave leaves less than an eighth of the next batch's ints unused when
+        // Waves keep reserves of the arena (see reserve_records) where its ints fit 32 bits.  A wave leaves less than an eighth of the next batch's ints unused when
         // it takes that one, and at the end holds less than one batch: the largest, or, as batches
         // double and hold an eighth of what the records between them took, 8 times its ints.
         unsigned long long nwaves = 0;
@@ -464,10 +472,7 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
         const unsigned long long ints = ucap_ints + ucap_ints / 7 + std::min<unsigned long long>(nwaves * kRecInts * kRecBatchMax, 10 * ucap_ints) +
                                         nwaves * kRecInts * 12;
         const unsigned long long ids = ucap_ints / 4 + 1 + std::min<unsigned long long>(nwaves * kRecBatchMax, ucap_ints) + nwaves * 8;
-        if ((ints >> 32) == 0) {
-            rec_batch = st->rec.ensure((size_t)ints * 4 + 256) == hipSuccess && st->rec_offs.ensure((size_t)ids * 8) == hipSuccess;
-            if (!rec_batch) (void)hipGetLastError();
-        }
+        rec_batch = !spare && (ints >> 32) == 0;
         rec_cap = rec_batch ? ints : ucap_ints;
         offs_cap = rec_batch ? ids : ucap_ints / 4 + 1;
         MBE_TRY(st->rec.ensure((size_t)rec_cap * 4 + 256));
@@ -540,11 +545,11 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
     const unsigned long long n_rec = out->count;
     const unsigned long long n_slots = rec_batch ? hacc[ACC_REC_INTS] >> 32 : hacc[ACC_RECORDS];
     if (n_rec == 0) return MBE_OK;
-    MBE_TRY(st->rec_tmp.ensure((size_t)n_slots * 2 * sizeof(RecordKey)));
+    MBE_TRY(st->rec_tmp.ensure((size_t)n_slots * (spare ? 8 : 2 * sizeof(RecordKey))));
     MBE_TRY(st->rec_lens.ensure((size_t)n_rec * 8));
     size_t canon_bytes = 0;
     MBE_TRY(canonical_records(st->rec.as<int32_t>(), st->rec_offs.as<unsigned long long>(), n_slots, n_rec,
-                              st->rec_tmp.as<RecordKey>(), st->rec_lens.as<unsigned long long>(), nullptr, nullptr,
+                              st->rec_tmp.p, spare, st->rec_lens.as<unsigned long long>(), nullptr, nullptr,
                               &canon_bytes, s));
     MBE_TRY(st->canon_tmp.ensure(canon_bytes));
     canon_bytes = st->canon_tmp.bytes;
@@ -554,7 +559,7 @@ int run(const mbe_graph *g, const mbe_options *opt_in, mbe_result *out, int32_t 
         dst = st->out_tmp.as<int32_t>();
     }
     MBE_TRY(canonical_records(st->rec.as<int32_t>(), st->rec_offs.as<unsigned long long>(), n_slots, n_rec,
-                              st->rec_tmp.as<RecordKey>(), st->rec_lens.as<unsigned long long>(), dst, st->canon_tmp.p,
+                              st->rec_tmp.p, spare, st->rec_lens.as<unsigned long long>(), dst, st->canon_tmp.p,
                               &canon_bytes, s));
     if (!ubuf_on_device) MBE_TRY(hipMemcpyAsync(ubuf, dst, (size_t)out->out_ints * 4, hipMemcpyDeviceToHost, s));
     MBE_TRY(hipStreamSynchronize(s));
@@ -1595,7 +1600,11 @@ int mbe_workspace_size(const mbe_graph *g, const mbe_options *opt, size_t *bytes
 
 int mbe_enumerate(const mbe_graph *g, const mbe_options *opt, mbe_result *out, int32_t *buf,
                   uint64_t buf_cap_ints, int32_t buf_on_device) {
-    return run(g, opt, out, buf, buf_cap_ints, buf_on_device, true);
+    const int rc = run(g, opt, out, buf, buf_cap_ints, buf_on_device, true);
+    if (rc != MBE_ERR_OUT_OF_MEMORY) return rc;
+    // The reserves of the record arena and the keys of its sort take more than a listing needs (per
+    // record 48 bytes of sort scratch against 16): where that was too much, once more without either.
+    return run(g, opt, out, buf, buf_cap_ints, buf_on_device, true, nullptr, false, nullptr, true);
 }
 
 const char *mbe_strerror(int code) {

@@ -291,7 +291,7 @@ struct RecordKey {
     unsigned long long off;
 };
 hipError_t canonical_records(int32_t *rec, unsigned long long *offs, unsigned long long n_slots,
-                             unsigned long long n_rec, RecordKey *keys, unsigned long long *lens,
+                             unsigned long long n_rec, void *scratch, bool small, unsigned long long *lens,
                              int32_t *out, void *temp, size_t *temp_bytes, hipStream_t s);
 
 }  // namespace mbe

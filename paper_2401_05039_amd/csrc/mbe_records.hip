@@ -67,14 +67,14 @@ __device__ __forceinline__ void sort_side(int32_t *a, int n, int l) {
 
 // Sorts the sides of every record and writes the sort keys of all index slots (those that hold no
 // record come last).  16 lanes per record: a thread per record, with its sides in memory, took 0.8 ms for
-// 516,620 records of 8 ints, this 0.15 ms.
+// 516,620 records of 8 ints, this 0.15 ms.  keys == NULL: none are written.
 __global__ void sort_sides_kernel(int32_t *rec, const unsigned long long *offs, unsigned long long n, RecordKey *keys) {
     const int l = (int)(threadIdx.x & 15u);
     const unsigned long long stride = ((unsigned long long)gridDim.x * blockDim.x) >> 4;
     for (unsigned long long i = ((unsigned long long)blockIdx.x * blockDim.x + threadIdx.x) >> 4; i < n; i += stride) {
         const unsigned long long off = offs[i];
         if (off == kNoRecord) {
-            if (l == 0) keys[i] = RecordKey{~0ull, kNoRecord};
+            if (l == 0 && keys) keys[i] = RecordKey{~0ull, kNoRecord};
             continue;
         }
         int32_t *r = rec + off;
@@ -82,12 +82,15 @@ __global__ void sort_sides_kernel(int32_t *rec, const unsigned long long *offs, 
         sort_side(r + 2, na, l);
         sort_side(r + 2 + na, nb, l);
         __threadfence_block();
-        if (l == 0) {
+        if (l == 0 && keys) {
             const unsigned int a0 = (unsigned int)r[2], a1 = na > 1 ? (unsigned int)r[3] + 1u : 0u;
             keys[i] = RecordKey{((unsigned long long)a0 << 32) | a1, off};
         }
     }
 }
+
+__device__ __forceinline__ unsigned long long offset_of(const RecordKey &k) { return k.off; }
+__device__ __forceinline__ unsigned long long offset_of(unsigned long long k) { return k; }
 
 // By the first two vertices of A, then by the whole of A.
 struct RecordLess {
@@ -95,11 +98,16 @@ struct RecordLess {
     __device__ bool operator()(const RecordKey &x, const RecordKey &y) const {
         if (x.head != y.head) return x.head < y.head;
         if (x.off == kNoRecord || y.off == kNoRecord) return false;  // (only both)
-        const int32_t *a = rec + x.off;
-        const int32_t *b = rec + y.off;
+        return after(x.off, y.off, 2);
+    }
+    __device__ bool operator()(unsigned long long x, unsigned long long y) const { return after(x, y, 0); }
+    // the same from the i-th vertex of A on
+    __device__ bool after(unsigned long long x, unsigned long long y, int i) const {
+        const int32_t *a = rec + x;
+        const int32_t *b = rec + y;
         const int na = a[0], nb = b[0];
         const int n = na < nb ? na : nb;
-        for (int i = 2; i < n; ++i) {
+        for (; i < n; ++i) {
             const int32_t p = a[2 + i], q = b[2 + i];
             if (p != q) return p < q;
         }
@@ -107,23 +115,25 @@ struct RecordLess {
     }
 };
 
-__global__ void lengths_kernel(const int32_t *rec, const RecordKey *keys, unsigned long long n,
+template <typename K>
+__global__ void lengths_kernel(const int32_t *rec, const K *keys, unsigned long long n,
                                unsigned long long *lens) {
     const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
     for (unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int32_t *r = rec + keys[i].off;
+        const int32_t *r = rec + offset_of(keys[i]);
         lens[i] = 2ull + (unsigned long long)r[0] + (unsigned long long)r[1];
     }
 }
 
 // one wave per record: copy it to its place in the output
-__global__ void gather_kernel(const int32_t *rec, const RecordKey *keys, const unsigned long long *dst,
+template <typename K>
+__global__ void gather_kernel(const int32_t *rec, const K *keys, const unsigned long long *dst,
                               unsigned long long n, int32_t *out) {
     const int lane = (int)__lane_id();
     const unsigned long long wave = ((unsigned long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const unsigned long long nwaves = ((unsigned long long)gridDim.x * blockDim.x) >> 6;
     for (unsigned long long i = wave; i < n; i += nwaves) {
-        const int32_t *r = rec + keys[i].off;
+        const int32_t *r = rec + offset_of(keys[i]);
         const unsigned long long len = 2ull + (unsigned long long)r[0] + (unsigned long long)r[1];
         int32_t *o = out + dst[i];
         for (unsigned long long q = lane; q < len; q += 64) o[q] = r[q];
@@ -137,16 +147,13 @@ int grid_for(unsigned long long n, int block) {
     return (int)g;
 }
 
-}  // namespace
-
-// rec: record arena; offs[n_slots]: record start offsets, kNoRecord where an index holds none, n_rec
-// others (overwritten); keys: 2 n_slots, lens: n_rec scratch; out: destination (sum of lengths ints).
-// With temp == NULL only *temp_bytes is set.
-hipError_t canonical_records(int32_t *rec, unsigned long long *offs, unsigned long long n_slots,
-                             unsigned long long n_rec, RecordKey *keys, unsigned long long *lens, int32_t *out,
-                             void *temp, size_t *temp_bytes, hipStream_t s) {
-    RecordLess less{rec};
-    RecordKey *sorted = keys + n_slots;
+// Sorts keys (n_slots of them, those of the n_rec records first) into sorted and writes the records to
+// out in that order; offs receives their places.  With temp == NULL only *temp_bytes is set.
+template <typename K>
+hipError_t sort_and_gather(const int32_t *rec, unsigned long long *offs, K *keys, K *sorted, unsigned long long n_slots,
+                           unsigned long long n_rec, unsigned long long *lens, int32_t *out, void *temp,
+                           size_t *temp_bytes, hipStream_t s) {
+    const RecordLess less{rec};
     size_t t_sort = 0, t_scan = 0;
     hipError_t e = rocprim::merge_sort(nullptr, t_sort, keys, sorted, (size_t)n_slots, less, s);
     if (e != hipSuccess) return e;
@@ -158,18 +165,36 @@ hipError_t canonical_records(int32_t *rec, unsigned long long *offs, unsigned lo
         return hipSuccess;
     }
     if (*temp_bytes < need) return hipErrorInvalidValue;
-    if (n_rec == 0) return hipSuccess;
-    hipLaunchKernelGGL(sort_sides_kernel, dim3(grid_for(n_slots * 16, 256)), dim3(256), 0, s, rec, offs, n_slots, keys);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     e = rocprim::merge_sort(temp, t_sort, keys, sorted, (size_t)n_slots, less, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lengths_kernel, dim3(grid_for(n_rec, 256)), dim3(256), 0, s, rec, sorted, n_rec, lens);
+    hipLaunchKernelGGL(lengths_kernel<K>, dim3(grid_for(n_rec, 256)), dim3(256), 0, s, rec, sorted, n_rec, lens);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // offs now receives the destination offsets of the sorted records
     e = rocprim::exclusive_scan(temp, t_scan, lens, offs, 0ull, (size_t)n_rec, rocprim::plus<unsigned long long>(), s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gather_kernel, dim3(grid_for(n_rec * 64, 256)), dim3(256), 0, s, rec, sorted, offs, n_rec, out);
+    hipLaunchKernelGGL(gather_kernel<K>, dim3(grid_for(n_rec * 64, 256)), dim3(256), 0, s, rec, sorted, offs, n_rec, out);
     return hipGetLastError();
+}
+
+}  // namespace
+
+// rec: record arena; offs[n_slots]: record start offsets, kNoRecord where an index holds none, n_rec
+// others (overwritten); scratch: 2 n_slots RecordKeys, or, with small, n_slots u64 (every index holds
+// a record then): the sort compares records by reading both, with a quarter of the scratch; lens:
+// n_rec scratch; out: destination (sum of lengths ints).  With temp == NULL only *temp_bytes is set.
+hipError_t canonical_records(int32_t *rec, unsigned long long *offs, unsigned long long n_slots,
+                             unsigned long long n_rec, void *scratch, bool small, unsigned long long *lens, int32_t *out,
+                             void *temp, size_t *temp_bytes, hipStream_t s) {
+    RecordKey *keys = small ? nullptr : static_cast<RecordKey *>(scratch);
+    if (temp != nullptr) {
+        if (n_rec == 0) return hipSuccess;
+        hipLaunchKernelGGL(sort_sides_kernel, dim3(grid_for(n_slots * 16, 256)), dim3(256), 0, s, rec, offs, n_slots, keys);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (small)
+        return sort_and_gather(rec, offs, offs, static_cast<unsigned long long *>(scratch), n_slots, n_rec, lens, out, temp,
+                               temp_bytes, s);
+    return sort_and_gather(rec, offs, keys, keys + n_slots, n_slots, n_rec, lens, out, temp, temp_bytes, s);
 }
 
 }  // namespace mbe

@@ -86,6 +86,57 @@ def test_record_paths(mbe, orc, nu, nv, p):
             assert mbe.decode_records(flat) == want["list"], kw
 
 
+_SHIM = r"""
+#include <dlfcn.h>
+#include <stddef.h>
+static size_t limit;
+static int refused;
+void shim_limit(size_t n) { limit = n; }
+int shim_refused(void) { return refused; }
+int hipMalloc(void **p, size_t n) {
+    static int (*real)(void **, size_t);
+    if (!real) real = (int (*)(void **, size_t))dlsym(dlopen("libamdhip64.so.7", RTLD_LAZY | RTLD_NOLOAD), "hipMalloc");
+    if (limit && n > limit) return ++refused, 2;  // hipErrorOutOfMemory
+    return real(p, n);
+}
+"""
+_SHORT_OF_MEMORY = r"""
+import ctypes, sys
+import numpy as np
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # found before the runtime's own hipMalloc
+shim.shim_limit.argtypes = [ctypes.c_size_t]
+import graphgen as gg
+import paper_2401_05039_amd as mbe
+n = 200_000
+i = np.arange(n)
+g = gg.from_edges(n, n, np.concatenate([i, i]), np.concatenate([i, (i + 1) % n]))  # one cycle
+want = [[1, 2, u, *sorted((u, (u + 1) % n))] for u in range(n)]
+want += [[2, 1, *sorted(((v - 1) % n, v)), v] for v in range(n)]
+want.sort(key=lambda r: r[2:2 + r[0]])
+want = np.array([x for r in want for x in r], dtype=np.int32)
+for limit in (28 * 2 * n, 0):  # sort keys are 32 bytes a record, everything else is below 24
+    shim.shim_limit(limit)
+    res, flat = mbe.mbe_enumerate(g, mbe.Options(grid=2), cap_ints=len(want))
+    assert res["count"] == 2 * n and np.array_equal(flat, want), limit
+    assert shim.shim_refused() == 1, limit
+print("listed")
+"""
+
+
+def test_listing_short_of_memory(tmp_path):
+    """A listing whose sort keys cannot be allocated is made with less scratch (the allocation is
+    refused on the host, in a process of its own)."""
+    import subprocess
+    import sys
+    (tmp_path / "shim.c").write_text(_SHIM)
+    so = str(tmp_path / "shim.so")
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-O1", "-o", so, str(tmp_path / "shim.c"), "-ldl"])
+    _say("short of memory")
+    r = subprocess.run([sys.executable, "-c", _SHORT_OF_MEMORY, so], capture_output=True, text=True, timeout=100,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0 and "listed" in r.stdout, (r.stdout, r.stderr)
+
+
 def test_workload1_golden(mbe):
     gold = json.load(open(os.path.join(GOLDEN, "workloads.json")))["config1"]
     _say("workload1 golden")
