@@ -1802,7 +1802,7 @@ struct WGShared {
     int vpub;            // mode 3: the third-level slot taken, and its epoch
     unsigned int vepoch;
     int vroot;           // modes 2 and 3: the arena slot that holds the top-level list
-    uint32_t t0;         // wall clock when the search of the current list began
+    uint32_t t0;         // wall clock when this workgroup began to search the current list
     int H;               // top-level items, and entries of the local universe, of the current task
     int us0;
     int tg, tk;          // graph and top-level rank of the current task
@@ -2343,6 +2343,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
                 sh->topf = rec->top;
                 sh->H = rec->H;
                 sh->us0 = rec->s0;
+                sh->t0 = (uint32_t)wall_clock64();
                 sh->claim = 0u;
                 sh->moved = 0u;
                 sh->published = 0;

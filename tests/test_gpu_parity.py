@@ -295,6 +295,43 @@ def test_first_holders(mbe, orc, nu, nv, p):
     _check(mbe, orc, gg.private_neighbours(nu, 3), f"private {nu}", side=1)
 
 
+def _heavy_candidate(nu, nv, p, twins):
+    """A random graph whose first-ranked candidate has so many rows equal to its own (they hold all
+    of N(x), so they are in no list of x's subtree); searched alone, its child list is the only work."""
+    g = gg.random_small(nu, nv, p, 5)
+    us, vs = g.edges()
+    deg = np.diff(g.u_off)
+    x = int(np.lexsort((np.arange(nu), deg))[0])
+    row = g.u_adj[g.u_off[x]:g.u_off[x + 1]]
+    us = np.concatenate([us] + [np.full(len(row), nu + k) for k in range(twins)])
+    return gg.from_edges(nu + twins, nv, us, np.concatenate([vs] + [row] * twins))
+
+
+# Classes of 1, 2 and 8 mask words; the list moves once it has been searched for 0.3 ms and others
+# wait.  even: no single item is most of the work (in the last graph the first item is).
+@pytest.mark.parametrize("nu,nv,p,twins,even", [(150, 180, 0.35, 3, True), (60, 400, 0.35, 0, True),
+                                                (60, 400, 0.35, 3, True), (50, 900, 0.35, 2, False)])
+def test_lists_read_by_other_workgroups(mbe, orc, nu, nv, p, twins, even):
+    """One top-level candidate, many workgroups: whatever another workgroup than its owner counts or
+    lists, it found in the owner's list."""
+    g = _heavy_candidate(nu, nv, p, twins)
+    _say("lists read by others", nu, nv, twins)
+    want = orc.mbea(g, side=1, rank_lo=0, rank_hi=1, want_list=True)
+    one = dict(side=1, root_lo=0, root_hi=1)
+    for kw in (dict(), dict(grid=48, wg_waves=2), dict(steal_k=3, wg_waves=4)):
+        res, loads = mbe.mbe_count_loads(g, mbe.Options(**one, **kw))
+        assert (res["count"], res["hash"]) == (want["count"], want["hash"]), kw
+        busy = (loads[:, 2] - loads[:, 1] - loads[:, 3]).astype(np.int64)  # ns at work
+        assert (busy > 50_000).sum() >= 2, (kw, np.sort(busy)[-4:])
+    alone, flat = mbe.mbe_enumerate(g, mbe.Options(steal_k=1, **one))
+    assert mbe.decode_records(flat) == want["list"]
+    for kw in (dict(), dict(steal_k=3), dict(diagnostics=True)):
+        res, flat = mbe.mbe_enumerate(g, mbe.Options(**one, **kw))
+        assert mbe.decode_records(flat) == want["list"], kw
+        if not kw and even:  # far more waves than one workgroup has: others wrote most of these records
+            assert res["kernel_ms"] < 0.6 * alone["kernel_ms"], (res["kernel_ms"], alone["kernel_ms"])
+
+
 @pytest.mark.parametrize("steal_k", [1, 2, 3])
 def test_stacks_that_run_out(mbe, orc, steal_k):
     """Nested child lists of up to 675-bit masks outgrow the wave stacks a new server starts with:
