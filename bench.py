@@ -212,13 +212,19 @@ def steal_ablation(mbe, dg, rng, steps=3):
 def prune_study(mbe, dg, rng, plain, steps=3):
     """The tree and search time under the pruning of section II-C (same answers): iMBEA's
     candidate pruning (prune = 1) and the pivot rule (prune = 2), both run by the generic-width
-    search, beside the plain tree of the fixed-width classes (plain: its diagnostics result)."""
+    search, beside the plain tree of the fixed-width classes (plain: its diagnostics result).
+    The times are of calls on a caller's workspace: on the library's own buffers a pruned call
+    without tallies is searched by the fixed-width classes, without the pruning."""
+    import torch
     lo, hi = rng if rng else (0, 0)
     out = {"plain": {"nodes": plain["nodes"], "nonmaximal": plain["nonmaximal"], "max_depth": plain["max_depth"]}}
     for name, mode in (("imbea", 1), ("pivot", 2)):
         d = mbe.mbe_count(dg, mbe.Options(prune=mode, diagnostics=1, root_lo=lo, root_hi=hi))
         assert (d["count"], d["hash"]) == (plain["count"], plain["hash"]), name
-        opt = mbe.Options(prune=mode, root_lo=lo, root_hi=hi)
+        size = mbe.mbe_workspace_size(dg, mbe.Options(prune=mode, root_lo=lo, root_hi=hi))
+        # (the generic-width search takes up to half of a workspace)
+        ws = torch.empty(2 * size + (64 << 20), dtype=torch.uint8, device="cuda")
+        opt = mbe.Options(prune=mode, root_lo=lo, root_hi=hi, workspace=ws)
         mbe.mbe_count(dg, opt)
         ks = [mbe.mbe_count(dg, opt)["kernel_ms"] for _ in range(steps)]
         out[name] = {"nodes": d["nodes"], "nonmaximal": d["nonmaximal"], "max_depth": d["max_depth"],

@@ -934,6 +934,24 @@ def test_prune_routes_agree(mbe, orc, prune, nu, nv, p, twins):
         assert [r[k] for k in ("count", "hash", "out_ints", "side")] == [want[k] for k in ("count", "hash", "out_ints", "side")]
 
 
+@pytest.mark.parametrize("prune", [1, 2])
+def test_pruned_search_lists(mbe, orc, prune):
+    """Listings made by the pruned wide search: with diagnostics every candidate's, without those of
+    candidates of more than 1024 neighbours."""
+    mixed = _with_covers(_with_twins(gg.random_small(40, 70, 0.2, 61), 12, 3), 10, 4)
+    for g, opts in ((_with_twins(gg.config1(), 15, 3), (dict(diagnostics=True),)),
+                    (_with_covers(gg.config1(), 15, 3), (dict(diagnostics=True),)),
+                    (mixed, (dict(diagnostics=True), dict(diagnostics=True, side=1, wg_waves=2, grid=3))),
+                    (gg.disjoint_union(gg.complete_minus_edge(4, 1500), mixed), (dict(), dict(diagnostics=True))),
+                    (_wide(0), (dict(), dict(diagnostics=True)))):
+        _say("pruned lists", prune, g.name)
+        want = orc.mbea(g, want_list=True)
+        for kw in opts:
+            res, flat = mbe.mbe_enumerate(g, mbe.Options(prune=prune, **kw))
+            assert (res["count"], res["hash"]) == (want["count"], want["hash"]), (g.name, kw)
+            assert mbe.decode_records(flat) == want["list"], (g.name, kw)
+
+
 def test_prune_rejected_where_unsupported(mbe):
     g = gg.crown(5)
     for call in (lambda: mbe.mbe_count_batch([g], mbe.Options(prune=True)),
