@@ -81,7 +81,7 @@ constexpr int kQReduce = 256;
 // candidates, in global scratch for longer ones.
 constexpr int kStuLds = 256;
 static_assert(2 * kStuLds >= 64 * 8, "P' masks of 64 entries fit the second half");
-constexpr int kWaveLds = 1024 + 8 * kQKeep + 4 * kStuLds + 32;  // LDS bytes per wave besides the histogram
+constexpr int kWaveLds = 768 + 8 * kQKeep + 4 * kStuLds + 32;  // LDS bytes per wave besides the histogram
 // The fixed-width classes keep a graph's rank bitmap and its popcount prefix in LDS, after the
 // waves' regions, when the bitmap has at most this many words (131,072 candidates); larger
 // graphs keep them in the workgroup's arena slot.
@@ -391,8 +391,8 @@ struct Ctx {
     uint32_t *stk;                    // this wave's stack
     uint32_t *stu;                    // a maximal node's Q' and P' positions in list order
     uint32_t *stu_l;                  // the same in this wave's LDS (lists of at most kStuLds entries)
-    lds_u32 *tl_first, *tl_cnt;       // this wave's LDS tables for narrow children
-    lds_u64 *tl_H;
+    lds_u32 *tl_cnt;                  // this wave's LDS list of candidates to test (64)
+    lds_u64 *tl_H;                    // this wave's LDS hash sums of a narrow child (64)
     lds_u64 *qk;                      // this wave's LDS list of Q' masks (kQKeep)
     lds_u64 *pm;                      // P' masks of a child list of at most 64 (the second half of stu_l)
     lds_u32 *hist;                    // this wave's LDS histogram
@@ -742,7 +742,7 @@ __device__ __forceinline__ uint64_t first_holders(const FrameState &F, const Fra
 // one's.
 template <bool DIAG, bool TB>
 __device__ __forceinline__ uint64_t check_chunk(const Ctx &c, const FrameState &F, const FrameView &v, int base,
-                                                uint64_t m, uint64_t hv, WaveAcc &acc, bool settle) {
+                                                uint64_t m, uint64_t hv, WaveAcc &acc) {
     const int ln = lane_id();
     const bool mine = (hv >> ln) & 1ull;
     const int words = min(v.nw, ((base + 63) >> 6) + 1);
@@ -762,7 +762,7 @@ __device__ __forceinline__ uint64_t check_chunk(const Ctx &c, const FrameState &
         const int lg = words > 32 ? 6 : 32 - __clz(words - 1);
         const int group = 1 << lg, per = 64 >> lg, nh = __popcll(hv), rk = __popcll(hv & lanes_below());
         const int sub = ln & (group - 1), grp = ln >> lg;
-        if (mine) c.tl_cnt[rk] = (uint32_t)ln;  // (the table space is free between child builds)
+        if (mine) c.tl_cnt[rk] = (uint32_t)ln;
         __builtin_amdgcn_wave_barrier();
         for (int done = 0; done < nh; done += per) {
             const bool on = done + grp < nh;
@@ -793,24 +793,22 @@ __device__ __forceinline__ uint64_t check_chunk(const Ctx &c, const FrameState &
                 dead = ((hb >> ((rk - done) << lg)) & (lg == 6 ? ~0ull : (1ull << group) - 1ull)) != 0ull;
         }
     }
-    if (settle) {
-        if (DIAG && dead) {
-            const int i = base + ln;
-            const uint64_t dx = deg_of(c, v.ids[i]);
-            uint64_t rs = 0;
-            for (uint64_t mm = m; mm; mm &= mm - 1ull)
-                rs += 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)(__ffsll((unsigned long long)mm) - 1))];
-            const uint64_t fw = F.fw - (2ull + dx);
-            acc.nodes += 1;
-            acc.nonmax += 1;
-            if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
-            acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + (uint64_t)__popcll(m));
-        }
-        // the row words up to the candidate (lists of up to 64: every row once)
-        if (TB && mine)
-            acc.dbytes += words == 1 ? 0ull : 8ull * (uint64_t)__popcll(m) * (uint64_t)(((base + ln) >> 6) + 1);
-        if (TB && ln == 0 && words == 1) acc.dbytes += 8ull * (uint64_t)F.rbits;
+    if (DIAG && dead) {
+        const int i = base + ln;
+        const uint64_t dx = deg_of(c, v.ids[i]);
+        uint64_t rs = 0;
+        for (uint64_t mm = m; mm; mm &= mm - 1ull)
+            rs += 2ull + (uint64_t)c.degl[root_pos(F, v, (uint32_t)(__ffsll((unsigned long long)mm) - 1))];
+        const uint64_t fw = F.fw - (2ull + dx);
+        acc.nodes += 1;
+        acc.nonmax += 1;
+        if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
+        acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + (uint64_t)__popcll(m));
     }
+    // the row words up to the candidate (lists of up to 64: every row once)
+    if (TB && mine)
+        acc.dbytes += words == 1 ? 0ull : 8ull * (uint64_t)__popcll(m) * (uint64_t)(((base + ln) >> 6) + 1);
+    if (TB && ln == 0 && words == 1) acc.dbytes += 8ull * (uint64_t)F.rbits;
     return __ballot(dead);
 }
 
@@ -818,8 +816,7 @@ __device__ __forceinline__ uint64_t check_chunk(const Ctx &c, const FrameState &
 // lanes still to be handled one by one: |R'| >= 2, and for one-word masks maximal (with records
 // on and vertices in no list, c.tfull, maximal candidates of |R'| = 1 too).
 template <int WF, bool DIAG, bool ENUM, bool TB = false>
-__device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &F, const FrameView &v, int base, WaveAcc &acc,
-                                bool settle = true) {
+__device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &F, const FrameView &v, int base, WaveAcc &acc) {
     const uint64_t t0 = DIAG ? clock64() : 0ull;
     const int ln = lane_id();
     const int i = base + ln;
@@ -842,7 +839,7 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
         for (int w = 0; w < WF; ++w)
             if (m[w]) b = 64 * w + __ffsll((unsigned long long)m[w]) - 1;
         own = v.first[b] == (uint32_t)i + 1u;
-        if (settle && own && here) {
+        if (own && here) {
             // L' = L u {every entry with bit b}: all of them sit at positions >= i
             const uint64_t sL = F.sL + v.H[b];
             acc.count += 1;
@@ -851,7 +848,7 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
             acc.out_ints += 3ull + (uint64_t)nL;
             if (ENUM) rp = root_pos(F, v, (uint32_t)b);
         }
-        if (DIAG && settle && (here || !own)) {
+        if (DIAG && (here || !own)) {
             acc.nodes += 1;
             if (!own) acc.nonmax += 1;
             if ((uint32_t)F.level > acc.max_depth) acc.max_depth = (uint32_t)F.level;
@@ -861,24 +858,24 @@ __device__ __forceinline__ uint64_t light_chunk(const Ctx &c, const FrameState &
             acc.bytes += 4ull * ((2ull + dx) + (rs < fw ? rs : fw) + (uint64_t)(F.nm - 1) + 1ull);
         }
         // first[b]; for a maximal node H[b], cnt[b], the R-side hash term (and orig[b])
-        if (TB && settle) acc.dbytes += 4ull + (own ? 20ull : 0ull);
+        if (TB) acc.dbytes += 4ull + (own ? 20ull : 0ull);
     }
-    if (TB && act && settle) acc.dbytes += 8ull * WF;  // the entry's mask
+    if (TB && act) acc.dbytes += 8ull * WF;  // the entry's mask
     uint64_t hv = __ballot(act && r >= 2);
     if (DIAG) acc.ph[PH_LIGHT] += clock64() - t0;
     if constexpr (WF == 1) {
         const uint64_t t1 = DIAG ? clock64() : 0ull;
         if (hv) {
             const uint64_t open = hv & ~first_holders(F, v, base);
-            if (TB && settle && ln == 0) acc.dbytes += 4ull * (uint64_t)F.rbits;
-            if (open) hv &= ~check_chunk<DIAG, TB>(c, F, v, base, m[0], open, acc, settle);
+            if (TB && ln == 0) acc.dbytes += 4ull * (uint64_t)F.rbits;
+            if (open) hv &= ~check_chunk<DIAG, TB>(c, F, v, base, m[0], open, acc);
         }
         if (DIAG) acc.ph[PH_CHECK] += clock64() - t1;
     }
     if (ENUM) {
         const uint64_t ob = __ballot(own);
         if (!here) hv |= ob;
-        else if (settle && ob) write_leaf_records(c, ob, rp, nL);
+        else if (ob) write_leaf_records(c, ob, rp, nL);
     }
     return hv;
 }
@@ -2067,16 +2064,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
     c.stu = reinterpret_cast<uint32_t *>(wv + a.lay.off_w_u);
     c.hist = lds_at<lds_u32>(lds_raw, sizeof(WGShared) + (size_t)wid * BITS * 4);
     {
-        // per wave: narrow-child tables first[64] cnt[64] (u32), H[64] (u64); kept Q' masks
+        // per wave: candidates to test (u32[64]), a narrow child's H (u64[64]), kept Q' masks, P'
+        // positions, the reserve of the record arena
         const size_t tb = sizeof(WGShared) + hist_region_bytes(BITS, nw) + (size_t)wid * kWaveLds;
-        c.tl_first = lds_at<lds_u32>(lds_raw, tb);
-        c.tl_cnt = c.tl_first + 64;
-        c.tl_H = lds_at<lds_u64>(lds_raw, tb + 512);
-        c.qk = lds_at<lds_u64>(lds_raw, tb + 1024);
-        c.stu_l = reinterpret_cast<uint32_t *>(lds_raw + tb + 1024 + 8 * kQKeep);
-        c.pm = lds_at<lds_u64>(lds_raw, tb + 1024 + 8 * kQKeep + 2 * kStuLds);
+        c.tl_cnt = lds_at<lds_u32>(lds_raw, tb);
+        c.tl_H = lds_at<lds_u64>(lds_raw, tb + 256);
+        c.qk = lds_at<lds_u64>(lds_raw, tb + 768);
+        c.stu_l = reinterpret_cast<uint32_t *>(lds_raw + tb + 768 + 8 * kQKeep);
+        c.pm = lds_at<lds_u64>(lds_raw, tb + 768 + 8 * kQKeep + 2 * kStuLds);
         if (ENUM && a.rec_batch) {
-            c.res = lds_at<lds_u64>(lds_raw, tb + 1024 + 8 * kQKeep + 4 * kStuLds);
+            c.res = lds_at<lds_u64>(lds_raw, tb + 768 + 8 * kQKeep + 4 * kStuLds);
             c.res[0] = 0ull;
             c.res[1] = 0ull;
             c.res[2] = 0ull;
@@ -3177,7 +3174,7 @@ struct WCtx {
     uint64_t *Rr;    // R' as positions of N(x) (records)
 };
 
-// Candidates [base, base + 64) of frame F: lanes with |R'| = 1 are settled (when settle), the
+// Candidates [base, base + 64) of frame F: lanes with |R'| = 1 are settled, the
 // lanes with |R'| >= 2 are returned.
 // IMB: the candidate pruning of section II-C (see heavy_wide); a single-bit candidate whose
 // bit is first held by an earlier candidate of the list (a twin, maximal as the first holder)
