@@ -3080,6 +3080,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !
     }
     // tallies of the last graph
     if (sh->graph >= 0) flush_acc<DIAG, TB>(acc, a.graphs[sh->graph].acc, sh);
+    wait_mem();  // (every wave's stores to the slot have arrived before it is handed on)
     __syncthreads();
     if (threadIdx.x == 0) {
         if (TB && a.wg_load) {
