@@ -329,7 +329,7 @@ def test_lists_read_by_other_workgroups(mbe, orc, nu, nv, p, twins, even):
         res, flat = mbe.mbe_enumerate(g, mbe.Options(**one, **kw))
         assert mbe.decode_records(flat) == want["list"], kw
         if not kw and even:  # far more waves than one workgroup has: others wrote most of these records
-            assert res["kernel_ms"] < 0.6 * alone["kernel_ms"], (res["kernel_ms"], alone["kernel_ms"])
+            assert res["kernel_ms"] < 0.75 * alone["kernel_ms"], (res["kernel_ms"], alone["kernel_ms"])
 
 
 @pytest.mark.parametrize("steal_k", [1, 2, 3])
