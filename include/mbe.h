@@ -217,8 +217,9 @@ int mbe_count(const mbe_graph *g, const mbe_options *opt, mbe_result *out);
  * stacks, sized from the largest 2-hop neighbourhood of a candidate) with its work-sharing
  * slots.  It runs the preparation (validation and ranking, which give the neighbourhood
  * bound) on the device but no search.  Later calls on a device start from the largest stack
- * room earlier ones needed, which is included.  mbe_enumerate adds its record staging:
- * about 12 bytes per int of buf_cap_ints plus the sort temporaries.  The memory stays with
+ * room earlier ones needed, which is included.  mbe_enumerate adds its record staging: about
+ * 7 bytes per int of buf_cap_ints (11 with a host buffer), 56 per record and 6 KiB per wave of
+ * the search; where that cannot be allocated, 6 (10) per int and 24 per record.  The memory stays with
  * the library (per device) for later calls.  Errors as mbe_count; MBE_ERR_INVALID_ARG if
  * bytes is NULL.  An empty side or zero edges gives 0.
  */

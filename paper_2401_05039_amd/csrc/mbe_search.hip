@@ -39,11 +39,12 @@
 //    and 10^6 edges: tests one node at a time, Q' as list entries with masks and shuffles through
 //    the LDS pipe 37.6 ms; the tests 64 at a time, Q' as rows (subsets of R' found by word ANDs
 //    when |R'| <= 6) and cross-lane moves on the vector pipe 21.0 ms.  Twelve top-level
-//    candidates of a 20,000 x 5,000 graph of 2M edges: 280 -> 68 ms.
+//    candidates of a 20,000 x 5,000 graph of 2M edges: 280 -> 68 ms.  (With shared lists read in
+//    place and every wave stopping where one runs out of stack 19.4 and 52 ms.)
 //
-//  * Second level (the paper's k = 2 subtrees): the waves of the workgroup claim 64-wide
-//    chunks of the top-level node's child list from an LDS counter; each wave then runs its
-//    own depth-first search on an explicit stack of frames (section III-B's goal: no
+//  * Second level (the paper's k = 2 subtrees): the waves of the workgroup claim the candidates
+//    of the top-level node's child list that need a full node, one at a time, from an LDS
+//    counter; each wave then runs its own depth-first search on an explicit stack of frames (section III-B's goal: no
 //    recursion and no allocation; frames are laid back to back in one preallocated array).
 //
 // Counts and hashes are commutative u64 sums, so results do not depend on which lane, wave
@@ -181,8 +182,10 @@ __device__ __forceinline__ uint32_t align2(uint32_t x) { return (x + 1u) & ~1u; 
 // Global atomics are performed in L2, so a plain load issued after them may still be served
 // from a stale line in this compute unit's vector L1, or overtake them.  After a phase that
 // builds data with global atomics (and its barrier, if other waves read it), every reading
-// wave waits for its memory operations and invalidates the L1.  The data involved is private
-// to one workgroup, hence on one compute unit and one L2: the L2 stays valid.
+// wave waits for its memory operations and invalidates the L1.  While data is built it is one
+// workgroup's own, hence on one compute unit and one L2: the L2 stays valid.  (A top-level list
+// that other workgroups read later is released and acquired at device scope, see move_top_list
+// and the helper's start in search_kernel; an arena slot that changes hands is released so too.)
 // Wait until this wave's memory operations are done, so that plain stores made by some
 // lanes are in place before other lanes load them.
 __device__ __forceinline__ void wait_mem() { __builtin_amdgcn_s_waitcnt(0); }
@@ -2006,12 +2009,13 @@ __device__ __forceinline__ bool find_shared_list(const SearchArgs &a, WGShared *
 }
 
 // The classes of up to eight mask words keep four waves per SIMD resident (two 8-wave
-// workgroups per compute unit): their register budget is capped at 128.  That spills some
-// state to scratch (up to about 90 bytes per lane in the production instances, several
-// hundred in the diagnostics instances), and still measured faster than 203-234 registers at
-// two waves per SIMD: power-law step 47.8 -> 39.1 ms,
-// skewed sample 1.76 -> 1.27 s.  The search waits on memory latency, and more resident waves
-// hide it.
+// workgroups per compute unit), diagnostics instances apart: their register budget is capped at
+// 128.  That spills some state to scratch: in the production instances 0, 36, 44 and 108 bytes per
+// lane (1, 2, 4 and 8 words), in the listing instances 44, 452, 112 and 548, mostly invariants of
+// the workgroup's task loop, which the search below a candidate does not read.  Capped measured
+// faster than 203-234 registers at two waves per SIMD: power-law step 47.8 -> 39.1 ms, skewed
+// sample 1.76 -> 1.27 s.  The search waits on memory latency, and more resident waves hide it.
+// (Uncapped, the diagnostics instances spill 24 to 64 bytes.)
 // TB (with DIAG and ENUM off): the production search, also tallying its design bytes.
 template <int W, bool DIAG, bool ENUM, bool TB = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(W <= 8 && !DIAG ? 4 : 2))) void search_kernel(SearchArgs a, int64_t lo, int64_t hi, unsigned int *counter) {
